@@ -165,8 +165,10 @@ int check_train(const bmdca_train_problem& p) {
 
 // The kernel sequence of one epoch (arguments already validated).  `epoch`
 // is used when ctl.epoch is null.
-int enqueue_train(const bmdca_train_problem& p, uint64_t epoch, const DevCtl& ctl,
+int enqueue_train(const bmdca_train_problem& p, uint64_t epoch, const DevCtl& ctl_in,
                   hipStream_t s) {
+  DevCtl ctl = ctl_in;
+  ctl.own_layout = true;
   const int N = (int)p.N, L = p.L, q = p.q;
   const int pr = p.prec & kPrecMask;
   const int gather = pick_gather(p.prec, L, q);

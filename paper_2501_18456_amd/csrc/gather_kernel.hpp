@@ -741,6 +741,12 @@ hipError_t launch_gather_heat_w8(int q, const GatherShape& gs, const GatherArgs&
 // most kGMidWaves waves)
 hipError_t launch_gather_heat_w12(int q, const GatherShape& gs, const GatherArgs& a);
 
+// ----- sampler_few.hip: heat-bath sweeps of few chains, a workgroup per chain,
+// reading J itself; gather_few: whether N chains on `cus` CUs take it
+constexpr int64_t kGFewPerCu = 16;  // workgroups per CU counted on at most
+bool gather_few(int64_t N, int L, int q, int64_t cus);
+hipError_t launch_gather_few(int q, const float* J, const GatherArgs& a, int64_t cus);
+
 // Sweeps of the gather form over the laid-out blocks Jt (q = 2..32).
 template <bool MH>
 hipError_t launch_gather_form(const float* h, const float* Jt, int8_t* chains, int64_t N, int L,

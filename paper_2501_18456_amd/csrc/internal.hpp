@@ -27,6 +27,8 @@ struct DevCtl {
   const int64_t* count = nullptr;   // live chains: only chains < min(N, *count) are swept
   bool keep_layout = false;         // gather form: the workspace already holds the
                                     // re-laid-out couplings of this J
+  bool own_layout = false;          // gather form: no later call reads the couplings that
+                                    // this one leaves in the workspace (training epochs)
 };
 
 // ----- sampler.hip

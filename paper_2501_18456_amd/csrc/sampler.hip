@@ -283,11 +283,19 @@ hipError_t launch_gibbs_gather(const float* h, const float* J, int8_t* chains, i
                                unsigned long long* flips_out, int32_t* dev_err, void* ws,
                                hipStream_t s, const DevCtl& ctl, bool metropolis) {
   float* Jt = static_cast<float*>(ws);
-  if (!ctl.keep_layout) {
+  const int64_t cus =
+      ctl.cu_share > 0 ? std::min<int64_t>(ctl.cu_share, device_cus()) : device_cus();
+  const bool few = !metropolis && gather_few(N, L, q, cus);
+  // few chains read J itself, but a caller that holds the workspace may pass
+  // it on with keep_layout
+  if (!ctl.keep_layout && !(few && ctl.own_layout)) {
     const size_t total = (size_t)L * L * q * gather_qp(q);
     const unsigned nb = (unsigned)std::min<size_t>(ceil_div(total, 256), 65536);
     hipLaunchKernelGGL(k_gather_layout, dim3(nb), dim3(256), 0, s, J, L, q, Jt, ctl.active);
   }
+  if (few)
+    return launch_gather_few(q, J, GatherArgs{h, Jt, chains, N, L, sweeps, seed, sweep_offset, beta,
+                                              flips_out, dev_err, s, &ctl}, cus);
   if (metropolis)
     return launch_gather_metropolis(h, Jt, chains, N, L, q, sweeps, seed, sweep_offset, beta,
                                     flips_out, dev_err, s, ctl);
