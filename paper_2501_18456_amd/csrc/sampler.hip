@@ -261,21 +261,55 @@ size_t gather_ws_bytes(int L, int q) {
 
 // Jt[i][j][b][a'] = J[(j*q + b)][(i*q + a')] for a' < q and j != i, else 0
 // (the block j = i is zero, so the sum over j may include it).
-__global__ void k_gather_layout(const float* __restrict__ J, int L, int q, float* __restrict__ Jt,
-                                const int32_t* __restrict__ active) {
+//
+// A workgroup re-lays out kLayRows rows (j, b) of kLaySites sites: every
+// thread writes whole quads, a wave 1 KB runs; the q floats a quad row reads
+// share their cache lines with the neighbour sites' of the same workgroup.
+// Bound by HBM, L^2 q (q + QP) 4 bytes.
+constexpr int kLayRows = 32, kLaySites = 8;
+
+template <int NQ>
+__global__ __launch_bounds__(256) void k_gather_layout(const float* __restrict__ J, int L, int q,
+                                                       float* __restrict__ Jt,
+                                                       const int32_t* __restrict__ active) {
   if (active && *active == 0) return;
-  const int QP = gather_qp(q);
-  const size_t total = (size_t)L * L * q * QP;
-  const size_t Lq = (size_t)L * q;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (size_t)gridDim.x * blockDim.x) {
-    const int a = (int)(e % QP);
-    const size_t r = e / QP;  // ((i*L + j)*q + b)
-    const int b = (int)(r % q);
-    const size_t ij = r / q;
-    const int j = (int)(ij % L), i = (int)(ij / L);
-    Jt[e] = (a < q && j != i) ? J[((size_t)j * q + b) * Lq + (size_t)i * q + a] : 0.0f;
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const uint32_t Lq = (uint32_t)(L * q);
+  const int r0 = blockIdx.x * kLayRows, i0 = blockIdx.y * kLaySites;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)J, (short)0, (int)(Lq * Lq * 4u), 0x00020000);  // at most 2^30 bytes
+  constexpr int kQuads = kLayRows * NQ;  // of one site
+  f4* out = reinterpret_cast<f4*>(Jt);
+#pragma unroll 4
+  for (int e = threadIdx.x; e < kLaySites * kQuads; e += 256) {
+    const int i = i0 + e / kQuads, k = e % kQuads;
+    const int r = r0 + k / NQ, v = k % NQ;
+    if (i >= L || r >= (int)Lq) continue;
+    const auto w = __builtin_amdgcn_raw_buffer_load_b128(
+        rs, (int)(((uint32_t)r * Lq + (uint32_t)(i * q + 4 * v)) * 4u), 0, 0);
+    const bool other = r < i * q || r >= i * q + q;
+    f4 x;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) x[a] = (other && 4 * v + a < q) ? __uint_as_float(w[a]) : 0.0f;
+    out[(size_t)i * Lq * NQ + (size_t)r * NQ + v] = x;
   }
+}
+
+static hipError_t launch_gather_layout(const float* J, int L, int q, float* Jt,
+                                       const int32_t* active, hipStream_t s) {
+  const dim3 grid((unsigned)ceil_div(L * q, kLayRows), (unsigned)ceil_div(L, kLaySites));
+  switch (gather_qp(q) / 4) {
+#define BMDCA_LAY(NQ)                                                                       \
+  case NQ:                                                                                  \
+    hipLaunchKernelGGL(k_gather_layout<NQ>, grid, dim3(256), 0, s, J, L, q, Jt, active);      \
+    break;
+    BMDCA_LAY(1) BMDCA_LAY(2) BMDCA_LAY(3) BMDCA_LAY(4)
+    BMDCA_LAY(5) BMDCA_LAY(6) BMDCA_LAY(7) BMDCA_LAY(8)
+#undef BMDCA_LAY
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_gibbs_gather(const float* h, const float* J, int8_t* chains, int64_t N, int L,
@@ -289,9 +323,8 @@ hipError_t launch_gibbs_gather(const float* h, const float* J, int8_t* chains, i
   // few chains read J itself, but a caller that holds the workspace may pass
   // it on with keep_layout
   if (!ctl.keep_layout && !(few && ctl.own_layout)) {
-    const size_t total = (size_t)L * L * q * gather_qp(q);
-    const unsigned nb = (unsigned)std::min<size_t>(ceil_div(total, 256), 65536);
-    hipLaunchKernelGGL(k_gather_layout, dim3(nb), dim3(256), 0, s, J, L, q, Jt, ctl.active);
+    const hipError_t e = launch_gather_layout(J, L, q, Jt, ctl.active, s);
+    if (e != hipSuccess) return e;
   }
   if (few)
     return launch_gather_few(q, J, GatherArgs{h, Jt, chains, N, L, sweeps, seed, sweep_offset, beta,
