@@ -119,10 +119,11 @@ hipError_t launch_profile_fields(const double* f1, int L, int q, float* h, int32
                                  hipStream_t s);
 
 // ----- reweight.hip
+constexpr int kRwRed = 256;  // workgroup sums of the weights
 struct ReweightPlan {
   int planes, words;
   int64_t Mpad;
-  size_t off_planes, off_red, total;
+  size_t off_planes, off_codes, off_red, total;
 };
 ReweightPlan plan_reweight(int64_t M, int L, int q);
 hipError_t launch_reweight(const int8_t* msa, int64_t M, int L, int q, int32_t T,
