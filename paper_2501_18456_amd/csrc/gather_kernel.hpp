@@ -747,6 +747,29 @@ constexpr int64_t kGFewPerCu = 16;  // workgroups per CU counted on at most
 bool gather_few(int64_t N, int L, int q, int64_t cus);
 hipError_t launch_gather_few(int q, const float* J, const GatherArgs& a, int64_t cus);
 
+// ----- sampler_free.hip, sampler_free_wide.hip, sampler_free_mh.hip: sweeps
+// by free-running waves (q <= 16, q > 16, Metropolis)
+hipError_t launch_free_heat(int q, const GatherShape& gs, const GatherArgs& a);
+hipError_t launch_free_heat_wide(int q, const GatherShape& gs, const GatherArgs& a);
+hipError_t launch_free_metropolis(int q, const GatherShape& gs, const GatherArgs& a);
+
+// Free-running waves where the loading wave (one more than the plan's) fits
+// and a site has enough chunk-steps to run ahead in.  Barriers -> free:
+//   fewer than kGPairChains chains per workgroup, three chunks or two of 16
+//   sites and more: q = 21, L = 30 0.64 -> 0.55 ms, q = 12, L = 100 1.35 ->
+//   1.15, q = 5, L = 250 3.16 -> 3.01; not with one chunk (q = 8, L = 60 0.66
+//   -> 0.69) or two short ones (q = 32, L = 16 0.44 -> 0.50);
+//   more chains, whose barriers come once in two steps: four chunks (q = 21,
+//   L = 50 1.63 -> 1.47; q = 12, L = 200 4.37 -> 4.30; q = 8, L = 400 even),
+//   not three (q = 21, L = 40, 20 000 chains 1.17 -> 1.23; q = 12, L = 120
+//   1.83 -> 1.87); Metropolis of q > 8 from two on (q = 21, L = 30, 20 000
+//   chains 0.59 -> 0.55; q = 5, L = 250 2.95 -> 3.00).
+inline bool gather_free(const GatherShape& gs, int q, bool mh) {
+  if (gs.waves >= kGMaxWaves) return false;
+  if (gs.cpb < kGPairChains) return gs.nchunk >= 3 || (gs.nchunk == 2 && gs.jc >= 16);
+  return gs.nchunk >= (mh && q > 8 ? 2 : 4);
+}
+
 // Sweeps of the gather form over the laid-out blocks Jt (q = 2..32).
 template <bool MH>
 hipError_t launch_gather_form(const float* h, const float* Jt, int8_t* chains, int64_t N, int L,
@@ -766,6 +789,10 @@ hipError_t launch_gather_form(const float* h, const float* Jt, int8_t* chains, i
   if (gs.waves == 0 || gs.ahead != 3) return hipErrorInvalidValue;
   const GatherArgs a{h, Jt, chains, N, L, sweeps, seed, sweep_offset, beta, flips_out, dev_err,
                      s, &ctl};
+  if (gather_free(gs, q, MH))
+    return MH        ? launch_free_metropolis(q, gs, a)
+           : q <= 16 ? launch_free_heat(q, gs, a)
+                     : launch_free_heat_wide(q, gs, a);
   if constexpr (!MH) {
     if (q <= 16 && gs.waves <= kGSmallWaves) return launch_gather_heat_w8(q, gs, a);
     if (q > 16 && gs.waves <= kGMidWaves) return launch_gather_heat_w12(q, gs, a);
