@@ -41,7 +41,7 @@ LDS_BYTES_PER_CLK = 256
 GATHER_TRAFFIC_SOURCES = ("paper_2501_18456_amd/csrc/gather_kernel.hpp",
                           "paper_2501_18456_amd/csrc/gather_plan.hpp",
                           "paper_2501_18456_amd/csrc/sampler.hip",
-                          "paper_2501_18456_amd/csrc/sampler_w12.hip",
+                          "paper_2501_18456_amd/csrc/gather_free.hpp",
                           "paper_2501_18456_amd/csrc/common.hpp")
 # workload -> bytes per launch: the gather kernel's 10-sweep launch and the
 # field kernel's 5-sweep launch of the precision form (L = 256, N = 20 000)

@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libbmdca.so")
 PEAKS = os.path.join(HERE, "libbmdca_peaks.so")  # measurement aid of bench.py only
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "sampler.hip", "sampler_mh.hip", "sampler_w8.hip", "sampler_w12.hip", "sampler_few.hip",
+SOURCES = ["api.hip", "sampler.hip", "sampler_mh.hip", "sampler_few.hip",
            "sampler_free.hip", "sampler_free_wide.hip", "sampler_free_mh.hip", "stats.hip", "learn.hip",
            "reweight.hip", "scoring.hip", "equilibrium.hip", "decimation.hip"]
 

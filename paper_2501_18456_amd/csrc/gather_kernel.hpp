@@ -54,13 +54,11 @@ namespace bmdca {
 //     u < exp(beta (H_i(a') - H_i(a))).  The staging of the blocks is the
 //     same as for the heat-bath draw.
 //
-// Synchronisation: one workgroup barrier per chunk-step.  Before it, each
-// wave waits for its share of the current chunk (vmcnt: at most the A - 1
-// younger chunks outstanding) and for its own LDS reads of the previous step
-// (lgkmcnt 0).  After it, the slot of the previous step is free for every
-// wave and receives the chunk A steps ahead.  A chain's tokens are read and
-// written only by its own lanes (one wave, LDS in order), so token updates
-// need no barrier.
+// Synchronisation: one workgroup barrier per two chunk-steps, before which each
+// wave waits for its share of the next two chunks and for its own LDS reads
+// (plans of 16 waves; the others replace the barriers, gather_free.hpp).  A
+// chain's tokens are read and written only by its own lanes (one wave, LDS in
+// order), so token updates need no barrier.
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -176,10 +174,8 @@ __device__ __forceinline__ int narrow_sum(int x, int base) {
   return t;
 }
 
-// MAXW: the most waves a workgroup of this instantiation may have (16, or 8
-// for plans of at most 8 waves: twice the registers per lane, 256).
-template <int Q, int IT, int LPC, bool MH, int MAXW, bool PAIR>
-__global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
+template <int Q, int IT, int LPC, bool MH>
+__global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_gather(
     const float* __restrict__ h, const float* __restrict__ Jt, int8_t* __restrict__ chains,
     int64_t N, int L, int jc, int nchunk, int m4, int ahead, int nload, int slot, int cpb,
     int sweeps, uint32_t k0, uint32_t k1, uint64_t sweep_offset, float beta,
@@ -202,25 +198,18 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
   constexpr int vL = (Q - 1) / 4, eL = (Q - 1) % 4;  // lane and slot of state q-1
   typedef float f4 __attribute__((ext_vector_type(4)));
   extern __shared__ __attribute__((aligned(16))) unsigned char g_smem[];
-  // chains per wave: 64 / LPC (narrow chains: the last 64 % LPC lanes of a
-  // wave hold no chain)
-  constexpr int CPW = 64 / LPC;
-  constexpr bool kNarrow = LPC < 8;
-  const int T = blockDim.x, CPB = kNarrow ? (T / 64) * CPW : T / LPC;
+  const int T = blockDim.x, CPB = T / LPC;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
-  const int p = kNarrow ? lane % LPC : lane & (LPC - 1), u = p / V, v = p % V;
-  const bool lane_ok = !kNarrow || lane < CPW * LPC;
-  // chain slot in the workgroup (the wide form keeps the plain expression:
-  // the per-wave one costs scalar registers that the wide kernels spill)
-  const int cb = kNarrow ? wid * CPW + lane / LPC : tid / LPC;
+  const int p = lane & (LPC - 1), u = p / V, v = p % V;
+  const int cb = tid / LPC;
   const int nslot = ahead + 1;
   float* ring = reinterpret_cast<float*>(g_smem);                             // [nslot][slot]
   uint32_t* tokw = reinterpret_cast<uint32_t*>(ring + (size_t)nslot * slot);  // [S][m4][CPB]
   unsigned char* tokb = reinterpret_cast<unsigned char*>(tokw);
   const int64_t c =
       count ? (int64_t)cb * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * cpb + cb;
-  const bool has_chain = lane_ok && cb < cpb;
+  const bool has_chain = cb < cpb;
   const bool active = has_chain && (c < N);
   const bool reader = has_chain && v < NQ;
   uint32_t cid = (uint32_t)c;
@@ -242,7 +231,7 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
     return tokb + ((size_t)((j % S) * m4 + (m >> 2)) * CPB + cb) * 4 + (m & 3);
   };
 
-  for (int k = lane_ok ? p : S * m4; k < S * m4; k += LPC) {  // dword k = (site group, 4 positions)
+  for (int k = p; k < S * m4; k += LPC) {  // dword k = (site group, 4 positions)
     const int uu = k / m4, mq = k % m4;
     uint32_t w = 0;
     for (int e = 0; e < 4; ++e) {
@@ -286,9 +275,8 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
     }
     if (++sl == nslot) sl = 0;
   };
-  // chunks in flight before the first step: `ahead` (one barrier per step),
-  // or two (paired steps)
-  for (int64_t t = 0; t < (PAIR ? 2 : ahead) && t < Tn; ++t) {
+  // two chunks in flight before the first step
+  for (int64_t t = 0; t < 2 && t < Tn; ++t) {
     if (loader) issue_chunk(pi, pk, psl);
     advance(pi, pk, psl);
   }
@@ -313,11 +301,10 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
   const int jcs = jc / S;  // positions per lane per chunk (multiple of 4)
   int i = 0, k = 0, sw = 0, csl = 0;
   // heat-bath draw: the four token dwords the next chunk-step's first group
-  // of 16 positions starts with, read one step ahead (software pipeline).
-  // In the 16-wave instantiation (128 VGPRs) only with one site group
-  // (q > 16): with several, the four live registers cost more in spills than
-  // the pipeline saves.
-  constexpr bool kPipeTok = !MH && (S == 1 || MAXW <= 8);
+  // of 16 positions starts with, read one step ahead (software pipeline), only
+  // with one site group (q > 16): with several, the four live registers cost
+  // more in spills than the pipeline saves.
+  constexpr bool kPipeTok = !MH && S == 1;
   const uint32_t* twl = tokw + (size_t)u * m4 * CPB + cb;
   uint32_t g_tok[4] = {0u, 0u, 0u, 0u};
   if (kPipeTok && reader) {  // first chunk-step (tokens written above by this wave)
@@ -332,7 +319,7 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
     }
   }
   for (int64_t t = 0; t < Tn; ++t) {
-    if constexpr (PAIR) {
+    {
       // even steps: chunks t and t + 1 (issued two steps ago) complete in
       // every wave after the barrier, and the slots of t - 2 and t - 1 are
       // free for t + 2 and t + 3; odd steps read chunk t without a barrier
@@ -353,24 +340,6 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
           }
         }
         __builtin_amdgcn_s_setprio(0);
-      }
-    } else {
-      // chunk t is complete once at most the younger issued chunks (ahead - 1
-      // of them, fewer at the end) are pending
-      const int64_t rest = Tn - 1 - t;
-      const int younger = rest < ahead - 1 ? (int)rest : ahead - 1;
-      compiler_fence();
-      if (younger >= 2)
-        wait_vm_lgkm0<2 * IT>();
-      else if (younger == 1)
-        wait_vm_lgkm0<IT>();
-      else
-        wait_vm_lgkm0<0>();
-      __builtin_amdgcn_s_barrier();
-      compiler_fence();
-      if (t + ahead < Tn) {
-        if (loader) issue_chunk(pi, pk, psl);
-        advance(pi, pk, psl);
       }
     }
     if (MH && k == 0) {
@@ -576,11 +545,7 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
           l[e] = ok ? beta * (hq[e] + acc[e]) : -INFINITY;
           mx = fmaxf(mx, l[e]);
         }
-        const int nbase = lane - p;  // first lane of the chain (narrow chains)
-        if constexpr (kNarrow)
-          mx = narrow_max<LPC>(mx, nbase);
-        else
-          mx = group_max<V>(mx);
+        mx = group_max<V>(mx);
         float P[4];
         float run_sum = 0.0f;
 #pragma unroll
@@ -591,17 +556,10 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
         }
         // inclusive scan of the quad sums over v; exclusive = shifted by one
         float inc, excl, Stot;
-        if constexpr (kNarrow) {
-          inc = narrow_scan(run_sum, lane, v);
-          excl = __shfl(inc, lane - 1, kWave);
-          if (v == 0) excl = 0.0f;
-          Stot = __shfl(excl + P[eL], nbase + vL, kWave);  // S_{q-1}
-        } else {
-          inc = group_scan<V>(run_sum, v);
-          excl = V > 1 ? dpp_f<kDppShr1>(inc) : 0.0f;
-          if (v == 0) excl = 0.0f;
-          Stot = group_bcast<V, vL>(excl + P[eL], v);  // S_{q-1}
-        }
+        inc = group_scan<V>(run_sum, v);
+        excl = V > 1 ? dpp_f<kDppShr1>(inc) : 0.0f;
+        if (v == 0) excl = 0.0f;
+        Stot = group_bcast<V, vL>(excl + P[eL], v);  // S_{q-1}
         if (!kKeepRnd || (i & 3) == 0)
           rnd = philox4x32_10(make_uint4((uint32_t)i >> 2, sg, cid, 0u), k0, k1);
         const float uz = word_to_uniform(pick_word(rnd, i & 3)) * Stot;
@@ -609,10 +567,7 @@ __global__ __launch_bounds__(MAXW * 64) void k_gibbs_gather(
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (v < NQ && 4 * v + e < Q - 1 && excl + P[e] <= uz) ++cnt;
-        if constexpr (kNarrow)
-          cnt = narrow_sum<LPC>(cnt, nbase);
-        else
-          cnt = group_sum<V>(cnt);
+        cnt = group_sum<V>(cnt);
         // every lane of the chain drew the same state: patch the token of
         // site i in the dwords read ahead for the next site's first chunk
         if (kPipeTok && reader && u == i % S) {
@@ -679,33 +634,13 @@ struct GatherArgs {
   const DevCtl* ctl;
 };
 
-template <int Q, bool MH, int MAXW>
+template <int Q, bool MH>
 hipError_t launch_gather_shape(const GatherShape& gs, const GatherArgs& a) {
-  // lanes per chain: the planner's rule for (q, draw), or narrow chains
-  // (heat-bath, 5..7 quads per row) where the planner takes them
-  constexpr int LP = gather_lanes(Q, !MH), LN = gather_narrow_lanes(Q, !MH);
-  if (gs.lpc != LP && (LN == 0 || gs.lpc != LN)) return hipErrorInvalidValue;
-  // the step schedule is a template parameter: with both in one kernel the
-  // compiler scheduled each of them worse (up to 9% slower)
-  auto pick = [&](auto lanes, auto paired) {
-    constexpr int LL = decltype(lanes)::value;
-    constexpr bool PP = decltype(paired)::value;
-    return gs.items == 31   ? k_gibbs_gather<Q, 31, LL, MH, MAXW, PP>
-           : gs.items == 16 ? k_gibbs_gather<Q, 16, LL, MH, MAXW, PP>
-                            : k_gibbs_gather<Q, 8, LL, MH, MAXW, PP>;
-  };
-  using LPt = std::integral_constant<int, LP>;
-  decltype(&k_gibbs_gather<Q, 8, LP, MH, MAXW, false>) kern = pick(LPt{}, std::false_type{});
-  if (gs.pair) kern = pick(LPt{}, std::true_type{});
-  if constexpr (LN > 0) {
-    using LNt = std::integral_constant<int, LN>;
-    if (gs.lpc == LN) {
-      kern = pick(LNt{}, std::false_type{});
-      if constexpr (!MH) {
-        if (gs.pair) kern = pick(LNt{}, std::true_type{});
-      }
-    }
-  }
+  constexpr int LP = gather_lanes(Q, !MH);
+  if (gs.lpc != LP) return hipErrorInvalidValue;
+  auto kern = gs.items == 31   ? k_gibbs_gather<Q, 31, LP, MH>
+              : gs.items == 16 ? k_gibbs_gather<Q, 16, LP, MH>
+                               : k_gibbs_gather<Q, 8, LP, MH>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)gs.lds);
   if (e != hipSuccess) return e;
@@ -717,12 +652,12 @@ hipError_t launch_gather_shape(const GatherShape& gs, const GatherArgs& a) {
   return hipGetLastError();
 }
 
-template <bool MH, int MAXW>
+template <bool MH>
 hipError_t launch_gather_switch(int q, const GatherShape& gs, const GatherArgs& a) {
   switch (q) {
 #define BMDCA_GQ(n) \
   case n:           \
-    return launch_gather_shape<n, MH, MAXW>(gs, a);
+    return launch_gather_shape<n, MH>(gs, a);
     BMDCA_GQ(2) BMDCA_GQ(3) BMDCA_GQ(4) BMDCA_GQ(5) BMDCA_GQ(6) BMDCA_GQ(7) BMDCA_GQ(8)
     BMDCA_GQ(9) BMDCA_GQ(10) BMDCA_GQ(11) BMDCA_GQ(12) BMDCA_GQ(13) BMDCA_GQ(14) BMDCA_GQ(15)
     BMDCA_GQ(16) BMDCA_GQ(17) BMDCA_GQ(18) BMDCA_GQ(19) BMDCA_GQ(20) BMDCA_GQ(21) BMDCA_GQ(22)
@@ -733,13 +668,6 @@ hipError_t launch_gather_switch(int q, const GatherShape& gs, const GatherArgs& 
       return hipErrorInvalidValue;
   }
 }
-
-// ----- sampler_w8.hip: heat-bath sweeps with MAXW = 8 (q <= 16, plans of at
-// most kGSmallWaves waves)
-hipError_t launch_gather_heat_w8(int q, const GatherShape& gs, const GatherArgs& a);
-// ----- sampler_w12.hip: heat-bath sweeps with MAXW = 12 (q > 16, plans of at
-// most kGMidWaves waves)
-hipError_t launch_gather_heat_w12(int q, const GatherShape& gs, const GatherArgs& a);
 
 // ----- sampler_few.hip: heat-bath sweeps of few chains, a workgroup per chain,
 // reading J itself; gather_few: whether N chains on `cus` CUs take it
@@ -753,22 +681,15 @@ hipError_t launch_free_heat(int q, const GatherShape& gs, const GatherArgs& a);
 hipError_t launch_free_heat_wide(int q, const GatherShape& gs, const GatherArgs& a);
 hipError_t launch_free_metropolis(int q, const GatherShape& gs, const GatherArgs& a);
 
-// Free-running waves where the loading wave (one more than the plan's) fits
-// and a site has enough chunk-steps to run ahead in.  Barriers -> free:
-//   fewer than kGPairChains chains per workgroup, three chunks or two of 16
-//   sites and more: q = 21, L = 30 0.64 -> 0.55 ms, q = 12, L = 100 1.35 ->
-//   1.15, q = 5, L = 250 3.16 -> 3.01; not with one chunk (q = 8, L = 60 0.66
-//   -> 0.69) or two short ones (q = 32, L = 16 0.44 -> 0.50);
-//   more chains, whose barriers come once in two steps: four chunks (q = 21,
-//   L = 50 1.63 -> 1.47; q = 12, L = 200 4.37 -> 4.30; q = 8, L = 400 even),
-//   not three (q = 21, L = 40, 20 000 chains 1.17 -> 1.23; q = 12, L = 120
-//   1.83 -> 1.87); Metropolis of q > 8 from two on (q = 21, L = 30, 20 000
-//   chains 0.59 -> 0.55; q = 5, L = 250 2.95 -> 3.00).
-inline bool gather_free(const GatherShape& gs, int q, bool mh) {
-  if (gs.waves >= kGMaxWaves) return false;
-  if (gs.cpb < kGPairChains) return gs.nchunk >= 3 || (gs.nchunk == 2 && gs.jc >= 16);
-  return gs.nchunk >= (mh && q > 8 ? 2 : 4);
-}
+// Free-running waves wherever a wave is left to load: plans of 16 waves (more
+// than 120 chains per workgroup in 8 lanes, 60 in 16) keep the barriers, which
+// need no wave of their own.  Barriers -> free at either end of the range, ms:
+// q = 12, L = 50, 6000 chains, 5 sweeps, 0.43 -> 0.33; q = 5, L = 400, 20 000
+// chains, 3 sweeps, 6.88 -> 6.58; 15 waves, one more loading: q = 16, L = 100,
+// 30 000 chains, 3 sweeps, 1.74 -> 1.37, q = 9, L = 60, 5 sweeps 0.89 -> 0.89,
+// Metropolis q = 21, L = 100, 10 sweeps 5.02 -> 4.38.
+constexpr int kGLoaders = 2;
+inline bool gather_free(const GatherShape& gs) { return gs.waves < kGMaxWaves; }
 
 // Sweeps of the gather form over the laid-out blocks Jt (q = 2..32).
 template <bool MH>
@@ -780,24 +701,16 @@ hipError_t launch_gather_form(const float* h, const float* Jt, int8_t* chains, i
   // takes workgroups of at most kGShareChains chains: more, smaller
   // workgroups let the largest models spread onto CUs the others free.
   const int64_t cus = ctl.cu_share > 0 ? std::min<int64_t>(ctl.cu_share, device_cus()) : device_cus();
-  GatherShape gs = ctl.cu_share > 0 ? gather_plan(N, L, q, cus, kGShareChains, !MH)
+  const GatherShape gs = ctl.cu_share > 0 ? gather_plan(N, L, q, cus, kGShareChains, !MH)
                                     : gather_plan(N, L, q, cus, kGMaxWaves * 8, !MH);
-  // On a CU share the other models' launches compete for L2 and the MALL, and
-  // the third chunk in flight pays more than the halved barriers (64 models
-  // trained together: 484.6 ms per epoch with paired steps, 460.7 without)
-  if (ctl.cu_share > 0) gs.pair = 0;
   if (gs.waves == 0 || gs.ahead != 3) return hipErrorInvalidValue;
   const GatherArgs a{h, Jt, chains, N, L, sweeps, seed, sweep_offset, beta, flips_out, dev_err,
                      s, &ctl};
-  if (gather_free(gs, q, MH))
+  if (gather_free(gs))
     return MH        ? launch_free_metropolis(q, gs, a)
            : q <= 16 ? launch_free_heat(q, gs, a)
                      : launch_free_heat_wide(q, gs, a);
-  if constexpr (!MH) {
-    if (q <= 16 && gs.waves <= kGSmallWaves) return launch_gather_heat_w8(q, gs, a);
-    if (q > 16 && gs.waves <= kGMidWaves) return launch_gather_heat_w12(q, gs, a);
-  }
-  return launch_gather_switch<MH, kGMaxWaves>(q, gs, a);
+  return launch_gather_switch<MH>(q, gs, a);
 }
 
 }  // namespace bmdca

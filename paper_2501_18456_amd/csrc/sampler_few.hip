@@ -345,18 +345,18 @@ FewShape few_plan(int64_t N, int L, int q, int64_t cus) {
 }  // namespace
 
 // Chains per CU up to which a workgroup per chain is the faster form.  The
-// gather form's visit costs its staging, L q QP floats, whatever the number of
-// chains (up to 32 per CU); here it costs the chains' rows.  Measured, us per
-// visit, here and there: q = 21, L = 100: 0.85 and 5.4 with 128 chains, 2.4 and
-// 5.4 with 2048, 4.7 and 5.5 with 4096, 8.7 and 5.4 with 8192; L = 400, 2048
-// chains 15.0 and 17.9, 4096 chains 29 and 18 (one workgroup per CU); q = 12, L
-// = 100: 1.4 and 2.6 with 2048, 2.8 and 2.7 with 4096; q = 5, L = 200: 1.2 and
-// 2.4 with 1024, 2.2 and 2.4 with 2048, 4.2 and 2.5 with 4096; q = 32, L = 100:
-// 4.8 and 13.9 with 4096, 9.4 and 13.3 with 8192.
+// gather form's visit costs at least its staging, L q QP floats, whatever the
+// number of chains (up to 24 per CU); here it costs the chains' rows.  Measured,
+// us per visit, here and there: q = 21, L = 120: 2.2 and 3.9 with 1280 chains,
+// 3.6 and 3.9 with 2816, 4.5 and 3.9 with 3328; L = 300 (one workgroup per CU)
+// 7.3 and 8.9 with 1280, 10.2 and 8.9 with 1792; q = 12, L = 120: 1.8 and 2.4
+// with 2304, L = 300: 4.5 and 4.9 with 1792, 6.2 and 5.0 with 2304; q = 5, L =
+// 120: 0.9 and 1.2 with 1280, L = 300: 2.1 and 2.4 with 1280, 2.7 and 2.4 with
+// 1536; q = 32, L = 120: 5.5 and 6.1 with 3072, 8.1 and 6.2 with 4608.
 bool gather_few(int64_t N, int L, int q, int64_t cus) {
   const FewShape f = few_plan(N, L, q, cus);
   if (f.fits == 0) return false;
-  const int64_t most = q <= 8 ? 6 : q <= 16 ? 10 : q <= 24 ? 14 : 24;
+  const int64_t most = q <= 8 ? 5 : q <= 16 ? 8 : q <= 24 ? 11 : 13;
   return N <= cus * (f.fits > 1 ? most : most / 2 + 1);
 }
 

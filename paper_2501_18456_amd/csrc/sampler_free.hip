@@ -9,7 +9,7 @@ hipError_t launch_free_heat(int q, const GatherShape& gs, const GatherArgs& a) {
   switch (q) {
 #define BMDCA_GQ(n) \
   case n:           \
-    return launch_free_waves<n, false>(gs, a);
+    return launch_free_shape<n, false>(gs, a);
     BMDCA_GQ(2) BMDCA_GQ(3) BMDCA_GQ(4) BMDCA_GQ(5) BMDCA_GQ(6) BMDCA_GQ(7) BMDCA_GQ(8)
     BMDCA_GQ(9) BMDCA_GQ(10) BMDCA_GQ(11) BMDCA_GQ(12) BMDCA_GQ(13) BMDCA_GQ(14) BMDCA_GQ(15)
     BMDCA_GQ(16)
