@@ -394,7 +394,7 @@ size_t bmdca_workspace_bytes(int32_t kind, int64_t MN, int32_t L, int32_t q, int
       return gibbs_bytes(MN, L, q);
     case BMDCA_WS_ENERGY:
       if (MN < 0) return 0;
-      return plan_energy(MN, L, q).total;
+      return plan_energy(MN, L, q, SIZE_MAX).wanted;
     case BMDCA_WS_DRAW:
       if (MN < 1) return 0;
       return draw_ws_bytes(MN);
@@ -480,7 +480,7 @@ int bmdca_energy(const float* h, const float* J, const int8_t* seqs, int64_t B, 
   BMDCA_REQUIRE(B >= 0 && B <= (int64_t)1 << 31, "B=%lld outside 0..2^31", (long long)B);
   if (B == 0) return BMDCA_OK;  // nothing to score; seqs, E and ws may be NULL
   BMDCA_REQUIRE(h && J && seqs && E && ws, "null pointer argument");
-  const EnergyPlan plan = plan_energy(B, L, q);
+  const EnergyPlan plan = plan_energy(B, L, q, ws_bytes);
   if (ws_bytes < plan.total)
     return fail(BMDCA_EWORKSPACE, "energy workspace %zu < %zu bytes", ws_bytes, plan.total);
   return hip_status(launch_energy(h, J, seqs, B, L, q, E, plan, ws, dev_err, (hipStream_t)stream),
@@ -493,7 +493,7 @@ int bmdca_energy_noalloc(const float* h, const float* J, const int8_t* seqs, int
   BMDCA_REQUIRE(B >= 0 && B <= (int64_t)1 << 31, "B=%lld outside 0..2^31", (long long)B);
   if (B == 0) return BMDCA_OK;  // nothing to score; seqs and E may be NULL
   BMDCA_REQUIRE(h && J && seqs && E, "null pointer argument");
-  const EnergyPlan plan = plan_energy(B, L, q);
+  const EnergyPlan plan = plan_energy(B, L, q, kEnergyScratchBytes);
   if (plan.total > kEnergyScratchBytes)
     return fail(BMDCA_EINVAL,
                 "energy_noalloc: B=%lld at L=%d needs %zu bytes of scratch, more than the "
@@ -511,7 +511,7 @@ int bmdca_energy_batch(const float* h, const float* J, const int8_t* seqs, int64
   BMDCA_TRY(check_model(L, q));
   BMDCA_REQUIRE(cap >= 1 && cap <= (int64_t)1 << 31, "cap=%lld outside 1..2^31", (long long)cap);
   BMDCA_REQUIRE(h && J && seqs && E && ws && n_live, "null pointer argument");
-  const EnergyPlan plan = plan_energy(cap, L, q);
+  const EnergyPlan plan = plan_energy(cap, L, q, ws_bytes);
   if (ws_bytes < plan.total)
     return fail(BMDCA_EWORKSPACE, "energy workspace %zu < %zu bytes", ws_bytes, plan.total);
   return hip_status(launch_energy(h, J, seqs, cap, L, q, E, plan, ws, dev_err,

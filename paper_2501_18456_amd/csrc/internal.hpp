@@ -136,9 +136,13 @@ struct EnergyPlan {
   int64_t Bpad;    // sequences padded to 64
   int64_t steps;   // (column chunk, row site) steps over all pairs i < j
   int parts;       // contiguous step ranges (a function of L only)
-  size_t off_xt, off_part, total;
+  bool split;      // a workgroup per sub-range of a range (same energies)
+  size_t off_xt, off_part;
+  size_t total;    // bytes needed
+  size_t wanted;   // bytes with which `split` is chosen where it is faster
 };
-EnergyPlan plan_energy(int64_t B, int L, int q);
+// ws_bytes: what the caller has.
+EnergyPlan plan_energy(int64_t B, int L, int q, size_t ws_bytes);
 // count (optional, device): only sequences < min(B, *count) are scored (the
 // launch is sized for B; E past the count is left as it is).
 hipError_t launch_energy(const float* h, const float* J, const int8_t* seqs, int64_t B, int L,

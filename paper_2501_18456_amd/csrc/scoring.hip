@@ -18,14 +18,33 @@ namespace bmdca {
 // or 1024 sequences (four per thread) and one contiguous range of steps; it stages
 // each tile in LDS once (double-buffered through registers) and every
 // sequence picks J[(i, s_i), (j, s_j)] for its own tokens.  A step's 16
-// terms are summed in FP32 in column order and the step sums in FP64 in step
+// terms are summed in FP32 in column order, the step sums of a sub-range (a
+// range has kEFine of them) in FP64 in step order and the sub-range sums in
 // order, one FP64 partial sum per (range, sequence); the finish adds the
-// fields and the partials in range order.
-// The ranges depend on L only, so a sequence's energy does not depend on the
-// rest of the batch (nor on the workgroup size).
+// fields and the partials in a fixed order.
+// Ranges and sub-ranges depend on L only, so a sequence's energy does not
+// depend on the rest of the batch, on the workgroup size or on the form below.
+//
+// Small batches (fewer than kESplitBlocks workgroups otherwise, and room for
+// the sums) take a workgroup per sub-range and, up to kEFewSeqs sequences, one
+// sequence per thread; the finish then adds the sub-range sums of each range
+// first.  A workgroup's steps follow each other (fetch a tile, store it, look
+// up), about 2 us each, so a small call takes their number: 1003 sequences at
+// L = 123, q = 21, 16 ranges of 34 steps 84 us, 128 sub-ranges of 4 16 us; whole
+// calls, L = 200, 3000 sequences 122 -> 46 us, L = 60, 20 000 124 -> 34, q = 5,
+// L = 100, 1000 80 -> 18.  Where the ranges fill the device, sub-range sums
+// would be traffic for nothing, and the lookups bound the call: 64 random
+// 4-byte reads of LDS take 8.7 cycles (L = 512, q = 21, 1e5 sequences 2.9 ms).
 // ---------------------------------------------------------------------------
 constexpr int kEJC = 16;
-constexpr int kESeq = 4;  // sequences per thread
+// Sequences per thread: eight where the tiles leave a CU one workgroup anyway
+// (q = 32, L = 300, 50 000 sequences 839 -> 656 us, q = 26 738 -> 613); where
+// two fit, the registers of eight would take the second one (q = 21, L = 512,
+// 1e5 sequences 2.91 -> 3.20 ms).
+constexpr int energy_seqs(int Q) { return Q > 24 ? 8 : 4; }
+constexpr int kEFine = 8;  // sub-ranges per range
+constexpr int64_t kESplitBlocks = 256;
+constexpr int64_t kEFewSeqs = 2048;
 // Threads per workgroup: 512 (2048 sequences) for q > 8, so that each staged
 // tile serves twice the lookups (a workgroup loads its own copy of every
 // tile; at q = 21 the tile stores were about 30% of the LDS traffic): L = 512,
@@ -74,8 +93,7 @@ __host__ __device__ inline int energy_rows(int jc, int L) {
   return min(jc * kEJC + kEJC - 1, L - 1);
 }
 
-EnergyPlan plan_energy(int64_t B, int L, int q) {
-  (void)q;
+EnergyPlan plan_energy(int64_t B, int L, int q, size_t ws_bytes) {
   EnergyPlan p{};
   p.Bpad = ceil_div(std::max<int64_t>(B, 1), 64) * 64;
   p.steps = 0;
@@ -84,19 +102,21 @@ EnergyPlan plan_energy(int64_t B, int L, int q) {
   size_t o = 0;
   p.off_xt = o;   o = align256(o + (size_t)L * p.Bpad);
   p.off_part = o; o = align256(o + sizeof(double) * (size_t)p.parts * p.Bpad);
-  p.total = o;
+  p.total = p.wanted = o;
+  if (ceil_div(p.Bpad, energy_threads(q) * energy_seqs(q)) * p.parts < kESplitBlocks) {
+    p.wanted = align256(p.off_part + sizeof(double) * (size_t)p.parts * kEFine * p.Bpad);
+    p.split = ws_bytes >= p.wanted;
+  }
   return p;
 }
 
-template <int Q>
-__global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(const float* __restrict__ J,
-                                                            const int8_t* __restrict__ XT,
-                                                            int64_t Bpad, int64_t B, int L,
-                                                            int64_t steps, int parts,
-                                                            double* __restrict__ part,
-                                                            const int64_t* __restrict__ count) {
+// KS: sequences per thread.  SPLIT: a workgroup per sub-range.
+template <int Q, int KS, bool SPLIT>
+__global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(
+    const float* __restrict__ J, const int8_t* __restrict__ XT, int64_t Bpad, int64_t B, int L,
+    int64_t steps, int parts, double* __restrict__ part, const int64_t* __restrict__ count) {
   constexpr int kEThreads = energy_threads(Q);
-  constexpr int kESeqBlock = kEThreads * kESeq;  // sequences per workgroup
+  constexpr int kESeqBlock = kEThreads * KS;  // sequences per workgroup
   if (count && *count < B) B = *count;  // live sequences of a launch sized for B
   if ((int64_t)blockIdx.x * kESeqBlock >= B) return;  // whole workgroup, before any barrier
   constexpr int kW = kEJC * Q;                                 // tile row length (16 Q floats)
@@ -107,13 +127,18 @@ __global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(const float*
   typedef float f4 __attribute__((ext_vector_type(4)));
   __shared__ __attribute__((aligned(16))) float tile[2][Q * kP];
   const int tid = threadIdx.x;
-  const int p = blockIdx.y;
-  const int64_t t0 = steps * p / parts, t1 = steps * (p + 1) / parts;
+  // the steps of the range and the end of its sub-range f
+  const int p = SPLIT ? blockIdx.y / kEFine : blockIdx.y;
+  const int64_t r0 = steps * p / parts, r1 = steps * (p + 1) / parts;
+  auto fine_end = [&](int k) { return r0 + (r1 - r0) * (k + 1) / kEFine; };
+  int f = SPLIT ? blockIdx.y % kEFine : 0;
+  const int64_t t0 = SPLIT ? fine_end(f - 1) : r0, t1 = SPLIT ? fine_end(f) : r1;
+  int64_t fend = fine_end(f);
   const int Lq = L * Q;
   const int64_t b0 = (int64_t)blockIdx.x * kESeqBlock;  // first sequence of the workgroup
-  int64_t bs[kESeq];
+  int64_t bs[KS];
 #pragma unroll
-  for (int k = 0; k < kESeq; ++k) bs[k] = b0 + tid + kEThreads * k;
+  for (int k = 0; k < KS; ++k) bs[k] = b0 + tid + kEThreads * k;
 
   // (jc, i) of step t0
   int jc = 0;
@@ -181,31 +206,51 @@ __global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(const float*
     }
   };
 
-  double acc[kESeq];
+  double acc[KS], tot[KS];  // of the sub-range, of the sub-ranges before it
 #pragma unroll
-  for (int k = 0; k < kESeq; ++k) acc[k] = 0.0;
-  int sj[kESeq][kEJC];
+  for (int k = 0; k < KS; ++k) acc[k] = tot[k] = 0.0;
+  auto step_done = [&](int64_t t) {  // the steps before t are in acc
+    while (!SPLIT && t == fend && f < kEFine) {
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        tot[k] += acc[k];
+        acc[k] = 0.0;
+      }
+      fend = fine_end(++f);
+    }
+  };
+  step_done(t0);  // empty sub-ranges
+  // the chunk's tokens times 4 (bytes into a tile row), four to a register: a
+  // lookup's address is one addition of a byte of it (64 registers of unpacked
+  // tokens left no room for a second workgroup per CU with 8 sequences)
+  uint32_t sj[KS][kEJC / 4];
   auto load_chunk = [&](int cjc) {
 #pragma unroll
     for (int jj = 0; jj < kEJC; ++jj) {
       const int j = cjc * kEJC + jj;
       const __amdgpu_buffer_rsrc_t rs = site_rsrc(min(j, L - 1));
 #pragma unroll
-      for (int k = 0; k < kESeq; ++k) sj[k][jj] = (j < L) ? tok_in(rs, k) : 0;
+      for (int k = 0; k < KS; ++k) {
+        const uint32_t t = (uint32_t)tok_in(rs, k) << (8 * (jj & 3) + 2);
+        sj[k][jj / 4] = (jj & 3) ? sj[k][jj / 4] | t : t;
+      }
     }
   };
-  auto row_tokens = [&](int(&s)[kESeq], int site) {
+  auto row_tokens = [&](int(&s)[KS], int site) {
     const __amdgpu_buffer_rsrc_t rs = site_rsrc(site);
 #pragma unroll
-    for (int k = 0; k < kESeq; ++k) s[k] = tok_in(rs, k) * kP;
+    for (int k = 0; k < KS; ++k) s[k] = tok_in(rs, k) * (4 * kP);
   };
   // The lookups of one step (row site si_, chunk cjc, LDS buffer buf): the
   // step's terms summed in FP32 in column order, then added to the FP64 sum.
-  auto lookups = [&](int si_, int cjc, const int(&srow)[kESeq], int buf) {
-    const float* tb = tile[buf];
-    float sf[kESeq];
+  auto lookups = [&](int si_, int cjc, const int(&srow)[KS], int buf) {
+    float sf[KS];
+    auto look = [&](int k, int jj) {  // J[(i, s_i), (j, s_j)] of sequence k
+      const uint32_t a = (uint32_t)srow[k] + ((sj[k][jj / 4] >> (8 * (jj & 3))) & 0xFFu);
+      return *(const float*)((const char*)tile[buf] + a + 4 * jj * Q);
+    };
 #pragma unroll
-    for (int k = 0; k < kESeq; ++k) sf[k] = 0.0f;
+    for (int k = 0; k < KS; ++k) sf[k] = 0.0f;
     // for q <= 8 a step whose columns all pair with the row site skips the
     // per-column tests (q = 5: 11% shorter; for larger q the tests cost
     // nothing and the second copy of the loop 1-4%)
@@ -213,19 +258,19 @@ __global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(const float*
 #pragma unroll
       for (int jj = 0; jj < kEJC; ++jj)
 #pragma unroll
-        for (int k = 0; k < kESeq; ++k) sf[k] += tb[srow[k] + jj * Q + sj[k][jj]];
+        for (int k = 0; k < KS; ++k) sf[k] += look(k, jj);
     } else {
 #pragma unroll
       for (int jj = 0; jj < kEJC; ++jj) {
         const int j = cjc * kEJC + jj;
         if (j > si_ && j < L) {  // uniform over the workgroup
 #pragma unroll
-          for (int k = 0; k < kESeq; ++k) sf[k] += tb[srow[k] + jj * Q + sj[k][jj]];
+          for (int k = 0; k < KS; ++k) sf[k] += look(k, jj);
         }
       }
     }
 #pragma unroll
-    for (int k = 0; k < kESeq; ++k) acc[k] += (double)sf[k];
+    for (int k = 0; k < KS; ++k) acc[k] += (double)sf[k];
   };
 
   // The tile of step t + 1 is fetched into registers during step t and
@@ -234,7 +279,7 @@ __global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(const float*
   // offsets from t0, B: odd), so the lookups never wait on a load issued in
   // their own step and no register copy waits for one.
   f4 v[kNQ];
-  int sA[kESeq], sB[kESeq];
+  int sA[KS], sB[KS];
   int iA = i, jA = jc, iB = i, jB = jc;
   advance(iB, jB);
   if (t0 < t1) {
@@ -253,6 +298,7 @@ __global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(const float*
     advance(iC, jC);
     if (t + 1 < t1) load_tile(v, iB, jB);
     lookups(iA, jA, sA, 0);
+    step_done(t + 1);
     if (t + 2 < t1) {
       row_tokens(sA, iC);
     }
@@ -267,6 +313,7 @@ __global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(const float*
     advance(iD, jD);
     if (t + 2 < t1) load_tile(v, iC, jC);
     lookups(iB, jB, sB, 1);
+    step_done(t + 2);
     if (t + 3 < t1) {
       row_tokens(sB, iD);
     }
@@ -281,45 +328,62 @@ __global__ __launch_bounds__(energy_threads(Q)) void k_energy_pairs(const float*
     jB = jD;
   }
 #pragma unroll
-  for (int k = 0; k < kESeq; ++k)
-    if (bs[k] < B) part[(size_t)p * Bpad + bs[k]] = acc[k];
+  for (int k = 0; k < KS; ++k)
+    if (bs[k] < B) part[(size_t)blockIdx.y * Bpad + bs[k]] = SPLIT ? acc[k] : tot[k];
 }
 
-__global__ void k_energy_finish(const float* __restrict__ h, const int8_t* __restrict__ XT,
-                                int64_t Bpad, int64_t B, int L, int q, int parts,
-                                const double* __restrict__ part, float* __restrict__ E,
-                                const int64_t* __restrict__ count) {
+// E = -(fields) - (partial sums).  Eight groups of a workgroup's threads share
+// the sites and the ranges of 64 sequences, an eighth of either each, in order;
+// their sums are added in order.  A thread's loads come in batches of 16
+// (tokens, then their fields; then partial sums), so one thread per sequence
+// waited for L / 8 of them in turn: L = 123, 1003 sequences 11 -> 4.6 us.
+// FINE: the sums of kEFine sub-ranges per range, added in order first.
+constexpr int kEGroups = 8;
+template <bool FINE>
+__global__ __launch_bounds__(64 * kEGroups) void k_energy_finish(
+    const float* __restrict__ h, const int8_t* __restrict__ XT, int64_t Bpad, int64_t B, int L,
+    int q, int parts, const double* __restrict__ part, float* __restrict__ E,
+    const int64_t* __restrict__ count) {
   if (count && *count < B) B = *count;
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  // loads in batches of 16 (tokens, then their fields; then partial sums),
-  // subtractions in site order, then in range order
+  if ((int64_t)blockIdx.x * 64 >= B) return;  // whole workgroup, before the barrier
+  __shared__ double sums[kEGroups][64];
+  const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int64_t b = (int64_t)blockIdx.x * 64 + lane;  // below Bpad
   double acc = 0.0;
-  int i = 0;
-  for (; i + 16 <= L; i += 16) {
+  // batches of 16 sites; past the group's last one that site again, not added
+  const int i1 = L * (g + 1) / kEGroups;
+  for (int i = L * g / kEGroups; i < i1; i += 16) {
     int t[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) t[u] = XT[(size_t)(i + u) * Bpad + b];
+    for (int u = 0; u < 16; ++u) t[u] = XT[(size_t)min(i + u, i1 - 1) * Bpad + b];
     float hv[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) hv[u] = h[(i + u) * q + (t[u] < 0 ? 0 : t[u])];
+    for (int u = 0; u < 16; ++u) hv[u] = h[min(i + u, i1 - 1) * q + (t[u] < 0 ? 0 : t[u])];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) acc -= (double)hv[u];
+    for (int u = 0; u < 16; ++u)
+      if (i + u < i1) acc -= (double)hv[u];
   }
-  for (; i < L; ++i) {
-    int t = XT[(size_t)i * Bpad + b];
-    if (t < 0) t = 0;
-    acc -= (double)h[i * q + t];
-  }
-  int p = 0;
-  for (; p + 16 <= parts; p += 16) {
-    double pv[16];
+  const int p1 = parts * (g + 1) / kEGroups;
+  constexpr int kR = FINE ? kEFine : 1, kN = 16 / kR;  // sums per range, ranges per batch
+  for (int p = parts * g / kEGroups; p < p1; p += kN) {
+    double pv[kN][kR];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) pv[u] = part[(size_t)(p + u) * Bpad + b];
+    for (int u = 0; u < kN; ++u)
 #pragma unroll
-    for (int u = 0; u < 16; ++u) acc -= pv[u];
+      for (int r = 0; r < kR; ++r) pv[u][r] = part[(size_t)(min(p + u, p1 - 1) * kR + r) * Bpad + b];
+#pragma unroll
+    for (int u = 0; u < kN; ++u) {
+      double x = 0.0;
+#pragma unroll
+      for (int r = 0; r < kR; ++r) x += pv[u][r];
+      if (p + u < p1) acc -= x;
+    }
   }
-  for (; p < parts; ++p) acc -= part[(size_t)p * Bpad + b];
+  sums[g][lane] = acc;
+  __syncthreads();
+  if (g != 0 || b >= B) return;
+#pragma unroll
+  for (int k = 1; k < kEGroups; ++k) acc += sums[k][lane];
   E[b] = (float)acc;
 }
 
@@ -327,9 +391,15 @@ template <int Q>
 static void launch_energy_q(const float* J, const int8_t* XT, int64_t B, int L,
                             const EnergyPlan& plan, double* part, hipStream_t s,
                             const int64_t* count) {
-  const dim3 grid((unsigned)ceil_div(B, energy_threads(Q) * kESeq), (unsigned)plan.parts);
-  hipLaunchKernelGGL(k_energy_pairs<Q>, grid, dim3(energy_threads(Q)), 0, s, J, XT, plan.Bpad, B, L,
-                     plan.steps, plan.parts, part, count);
+  constexpr int T = energy_threads(Q);
+  constexpr int KS = energy_seqs(Q);
+  const int seqs = plan.split && B <= kEFewSeqs ? 1 : KS;
+  auto kern = !plan.split ? k_energy_pairs<Q, KS, false>
+              : seqs == 1 ? k_energy_pairs<Q, 1, true>
+                          : k_energy_pairs<Q, KS, true>;
+  const dim3 grid((unsigned)ceil_div(B, T * seqs), (unsigned)(plan.parts * (plan.split ? kEFine : 1)));
+  hipLaunchKernelGGL(kern, grid, dim3(T), 0, s, J, XT, plan.Bpad, B, L, plan.steps, plan.parts, part,
+                     count);
 }
 
 hipError_t launch_energy(const float* h, const float* J, const int8_t* seqs, int64_t B, int L,
@@ -358,8 +428,9 @@ hipError_t launch_energy(const float* h, const float* J, const int8_t* seqs, int
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_energy_finish, dim3((unsigned)ceil_div(B, 256)), dim3(256), 0, s, h, XT,
-                     plan.Bpad, B, L, q, plan.parts, part, E, count);
+  hipLaunchKernelGGL(plan.split ? k_energy_finish<true> : k_energy_finish<false>,
+                     dim3((unsigned)ceil_div(B, 64)), dim3(64 * kEGroups), 0, s, h, XT, plan.Bpad, B,
+                     L, q, plan.parts, part, E, count);
   return hipGetLastError();
 }
 
