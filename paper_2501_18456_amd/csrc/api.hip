@@ -528,11 +528,8 @@ int bmdca_mutant_scan_batch(const float* h, const float* J, const int8_t* wt, in
   if (ws_bytes < gibbs_bytes(cap, L, q))
     return fail(BMDCA_EWORKSPACE, "mutant workspace %zu < %zu bytes", ws_bytes,
                 gibbs_bytes(cap, L, q));
-  hipStream_t s = (hipStream_t)stream;
-  float* H = static_cast<float*>(ws);
-  BMDCA_TRY(hip_status(launch_local_fields(h, J, wt, cap, L, q, H, nullptr, s, nullptr, n_live),
-                       "mutant_batch/fields"));
-  return hip_status(launch_mutant_delta(H, wt, cap, L, q, dE, s, n_live), "mutant_batch/delta");
+  return hip_status(launch_mutant_scan(h, J, wt, cap, L, q, dE, (hipStream_t)stream, n_live),
+                    "mutant_batch");
 }
 
 int bmdca_sample_tick(const float* h, const float* J, int8_t* chains, int64_t cap,
@@ -782,10 +779,7 @@ int bmdca_single_mutant_scan(const float* h, const float* J, const int8_t* wt, i
   if (ws_bytes < gibbs_bytes(B, L, q))
     return fail(BMDCA_EWORKSPACE, "mutant workspace %zu < %zu bytes", ws_bytes,
                 gibbs_bytes(B, L, q));
-  hipStream_t s = (hipStream_t)stream;
-  float* H = static_cast<float*>(ws);
-  BMDCA_TRY(hip_status(launch_local_fields(h, J, wt, B, L, q, H, nullptr, s), "mutant/fields"));
-  return hip_status(launch_mutant_delta(H, wt, B, L, q, dE, s), "mutant/delta");
+  return hip_status(launch_mutant_scan(h, J, wt, B, L, q, dE, (hipStream_t)stream), "mutant");
 }
 
 int bmdca_apc_frobenius(const float* J, int32_t L, int32_t q, int32_t gap, float* F,

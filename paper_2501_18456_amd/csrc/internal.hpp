@@ -35,10 +35,9 @@ struct DevCtl {
 hipError_t launch_init_chains(int8_t* chains, int64_t N, int L, int q, uint64_t seed,
                               hipStream_t s);
 // H[c][r] = h[r] + sum_{k != r/q} J[(k, chains[c][k])][r] for c < N.
-// count (optional, device): only chains < min(N, *count).
 hipError_t launch_local_fields(const float* h, const float* J, const int8_t* chains, int64_t N,
                                int L, int q, float* H, int32_t* dev_err, hipStream_t s,
-                               const int32_t* active = nullptr, const int64_t* count = nullptr);
+                               const int32_t* active = nullptr);
 hipError_t launch_gibbs_sweeps(const float* J, int8_t* chains, float* H, int64_t N, int L, int q,
                                int sweeps, uint64_t seed, uint64_t sweep_offset, float beta,
                                unsigned long long* flips_out, hipStream_t s,
@@ -148,8 +147,8 @@ EnergyPlan plan_energy(int64_t B, int L, int q, size_t ws_bytes);
 hipError_t launch_energy(const float* h, const float* J, const int8_t* seqs, int64_t B, int L,
                          int q, float* E, const EnergyPlan& plan, void* ws, int32_t* dev_err,
                          hipStream_t s, const int64_t* count = nullptr);
-hipError_t launch_mutant_delta(const float* H, const int8_t* wt, int64_t B, int L, int q,
-                               float* dE, hipStream_t s, const int64_t* count = nullptr);
+hipError_t launch_mutant_scan(const float* h, const float* J, const int8_t* wt, int64_t B, int L,
+                              int q, float* dE, hipStream_t s, const int64_t* count = nullptr);
 size_t apc_ws_bytes(int L);
 hipError_t launch_apc(const float* J, int L, int q, int gap, float* F, float* Fapc, void* ws,
                       hipStream_t s);

@@ -51,7 +51,6 @@ __global__ __launch_bounds__(256) void k_local_fields(const float* __restrict__ 
                                                       int L, int q, float* __restrict__ H,
                                                       int32_t* dev_err,
                                                       const int32_t* __restrict__ active,
-                                                      const int64_t* __restrict__ count,
                                                       int64_t g0, int wq) {
   if (active && *active == 0) return;
   // Workgroups are numbered so that each XCD runs a contiguous range of the
@@ -64,7 +63,6 @@ __global__ __launch_bounds__(256) void k_local_fields(const float* __restrict__ 
   const int64_t g = g0 + (int64_t)(xcd * per + min(xcd, nwg % 8u) + f / 8u);
   const int64_t c = g % N;
   const int yb = (int)(g / N);
-  if (count && c >= *count) return;  // whole workgroup, before any barrier
   extern __shared__ int rowbase[];  // L entries: (k*q + s_k)
   const int Lq = L * q;
   for (int k = threadIdx.x; k < L; k += blockDim.x) {
@@ -111,7 +109,7 @@ __global__ __launch_bounds__(256) void k_local_fields(const float* __restrict__ 
 
 hipError_t launch_local_fields(const float* h, const float* J, const int8_t* chains, int64_t N,
                                int L, int q, float* H, int32_t* dev_err, hipStream_t s,
-                               const int32_t* active, const int64_t* count) {
+                               const int32_t* active) {
   const int Lq = L * q;
   // column blocks of equal width, wq quads (at most 256), so that every XCD's
   // range of workgroups holds the same work (a ragged last block left whole
@@ -123,7 +121,7 @@ hipError_t launch_local_fields(const float* h, const float* J, const int8_t* cha
   const int64_t nwg = N * nyb, chunk = (int64_t)1 << 22;
   for (int64_t g0 = 0; g0 < nwg; g0 += chunk) {
     hipLaunchKernelGGL(k_local_fields, dim3((unsigned)std::min(chunk, nwg - g0)), dim3(bs),
-                       sizeof(int) * L, s, h, J, chains, N, L, q, H, dev_err, active, count, g0, wq);
+                       sizeof(int) * L, s, h, J, chains, N, L, q, H, dev_err, active, g0, wq);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

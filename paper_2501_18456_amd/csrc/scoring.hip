@@ -437,28 +437,134 @@ hipError_t launch_energy(const float* h, const float* J, const int8_t* seqs, int
 // ---------------------------------------------------------------------------
 // Single mutants: dE[b][i*q+a] = -(H[b][i*q+a] - H[b][i*q+wt_i]), with H the
 // wild type's local fields (h + sum_{j != i} J_ij(., wt_j)).
+// Columns go in blocks of up to 256 / q whole sites, four consecutive columns
+// per lane; the L coupling rows in eighths, each summed in order (FP32), the
+// eighths added to h in order.  A column's own site is left out by a select on
+// the sum, so no row has a special case.
+//   SPLIT: a workgroup per (block, wild type), one wave per eighth.  What bounds
+//   a few wild types is the latency of the row loads: with all rows in one
+//   thread, four in flight, and the differences in a launch of their own, one
+//   wild type at L = 256, q = 21 took 21.7 + 4.1 us, now 7.1; 16 at L = 512 whole
+//   calls 65 -> 30 us.
+//   Otherwise a wave per (block, wild type), four wild types per workgroup.
+// With kMSplit workgroups or more, or eighths of few rows, the split form's row
+// addresses and exchange cost more than its latency saves: L = 512, 64 wild
+// types (2752) 102 us split, 78 not; L = 100, 150 (1350) 22.5 and 18; L = 256,
+// 64 (1408) 34.7 and 34.8.  Then, ROWS = 8 in flight while there are few waves
+// and many rows (L = 512, 64: 78 us, with four 83), else four (L = 100, 1000:
+// 49 us, with eight 67).
+// The sums are the same, so dE does not depend on the batch.
 // ---------------------------------------------------------------------------
-__global__ void k_mutant_delta(const float* __restrict__ H, const int8_t* __restrict__ wt,
-                               int64_t B, int L, int q, float* __restrict__ dE,
-                               const int64_t* __restrict__ count) {
-  if (count && *count < B) B = *count;
-  const int64_t Lq = (int64_t)L * q;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= B * Lq) return;
-  const int64_t b = idx / Lq;
-  const int r = (int)(idx % Lq);
-  const int i = r / q;
-  int w = wt[b * L + i];
-  if (w < 0 || w >= q) w = 0;  // flagged by the field build
-  const float* Hb = H + b * Lq;
-  dE[idx] = (r == i * q + w) ? 0.0f : -(Hb[r] - Hb[i * q + w]);
+constexpr int kMParts = 8;
+constexpr int64_t kMSplit = 1536;
+template <bool SPLIT, int ROWS>
+__global__ __launch_bounds__(SPLIT ? 64 * kMParts : 256) void k_mutant_scan(
+    const float* __restrict__ h, const float* __restrict__ J, const int8_t* __restrict__ wt,
+    int64_t B, int L, int q, int sites, int64_t g0, float* __restrict__ dE,
+    const int64_t* __restrict__ count) {
+  // contiguous (column block, wild type) ranges per XCD, wild type fastest, as
+  // in k_local_fields: rows that several wild types share come from the XCD's L2
+  constexpr int kPer = SPLIT ? 1 : 4;  // wild types per workgroup
+  const uint32_t nwg = gridDim.x, f = blockIdx.x, xcd = f % 8u, per = nwg / 8u;
+  const int64_t g = g0 + (int64_t)(xcd * per + min(xcd, nwg % 8u) + f / 8u);
+  const int64_t groups = ceil_div(B, kPer);
+  const int lane = threadIdx.x % 64;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int64_t b = g % groups * kPer + (SPLIT ? 0 : w);
+  if (b >= B || (count && b >= *count)) return;  // SPLIT: whole workgroup, before any barrier
+  const int s0 = (int)(g / groups) * sites, s1 = min(s0 + sites, L);  // this block's sites
+  const int c0 = s0 * q, nc = (s1 - s0) * q, Lq = L * q;              // and columns, at most 256
+  __shared__ float part[SPLIT ? kMParts : 1][256];
+  __shared__ float fields[kPer][256];
+  float* H = fields[SPLIT ? 0 : w];
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  int site[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) site[e] = (c0 + 4 * lane + e) / q;
+  // lanes past the block load from past the row's end: 0
+  const int off = 4 * lane < nc ? (c0 + 4 * lane) * (int)sizeof(float) : Lq * (int)sizeof(float);
+  auto eighth = [&](int p, float(&acc)[4]) {
+    const int k1 = L * (p + 1) / kMParts;
+    for (int kc = L * p / kMParts; kc < k1; kc += 64) {
+      const int n = min(64, k1 - kc), kl = kc + min(lane, n - 1);
+      const uint64_t row = (uint64_t)(kl * q + checked_token(wt[b * L + kl], q, nullptr)) * Lq * 4u;
+      for (int r = 0; r < n; r += ROWS) {
+        u4 x[ROWS];
+#pragma unroll
+        for (int e = 0; e < ROWS; ++e) {  // past the end the last row again, not added
+          const int k = min(r + e, n - 1);
+          const uint64_t at = (uint32_t)__builtin_amdgcn_readlane((int)row, k) |
+                              (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(row >> 32), k) << 32;
+          const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+              (void*)(reinterpret_cast<const char*>(J) + at), (short)0, Lq * (int)sizeof(float),
+              0x00020000);
+          x[e] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < ROWS; ++e) {
+          const bool over = r + e >= n;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const float sum = acc[c] + __uint_as_float(x[e][c]);
+            acc[c] = over || kc + r + e == site[c] ? acc[c] : sum;
+          }
+        }
+      }
+    }
+  };
+  auto write = [&](int c) {
+    const int i = c / q;
+    const int a = checked_token(wt[b * L + s0 + i], q, nullptr);
+    dE[b * Lq + c0 + c] = c == i * q + a ? 0.0f : -(H[c] - H[i * q + a]);
+  };
+  if constexpr (SPLIT) {
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    eighth(w, acc);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) part[w][4 * lane + e] = acc[e];
+    __syncthreads();
+    const int c = threadIdx.x;
+    if (c < nc) {
+      float x = h[c0 + c];
+#pragma unroll
+      for (int p = 0; p < kMParts; ++p) x += part[p][c];
+      H[c] = x;
+    }
+    __syncthreads();
+    if (c < nc) write(c);
+  } else {
+    float x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = 4 * lane + e < nc ? h[c0 + 4 * lane + e] : 0.0f;
+    for (int p = 0; p < kMParts; ++p) {
+      float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      eighth(p, acc);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] += acc[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) H[4 * lane + e] = x[e];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    for (int c = lane; c < nc; c += 64) write(c);
+  }
 }
 
-hipError_t launch_mutant_delta(const float* H, const int8_t* wt, int64_t B, int L, int q,
-                               float* dE, hipStream_t s, const int64_t* count) {
-  const int64_t total = B * (int64_t)L * q;
-  hipLaunchKernelGGL(k_mutant_delta, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, s, H, wt,
-                     B, L, q, dE, count);
+hipError_t launch_mutant_scan(const float* h, const float* J, const int8_t* wt, int64_t B, int L,
+                              int q, float* dE, hipStream_t s, const int64_t* count) {
+  // blocks of equal width, so that every XCD's range holds the same work
+  const int sites = (int)ceil_div(L, ceil_div(L, 256 / q));
+  const int64_t blocks = ceil_div(L, sites);
+  const bool split = B * blocks <= std::min<int64_t>(kMSplit, 6 * L);
+  auto kern = split                            ? k_mutant_scan<true, 16>
+              : B * blocks <= 4096 && L >= 200 ? k_mutant_scan<false, 8>
+                                               : k_mutant_scan<false, 4>;
+  // one launch per 2^22 workgroups (a grid dimension holds fewer than 2^32 work-items)
+  const int64_t nwg = ceil_div(B, split ? 1 : 4) * blocks, chunk = (int64_t)1 << 22;
+  for (int64_t g0 = 0; g0 < nwg; g0 += chunk)
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::min(chunk, nwg - g0)),
+                       dim3(split ? 64 * kMParts : 256), 0, s, h, J, wt, B, L, q, sites, g0, dE, count);
   return hipGetLastError();
 }
 
