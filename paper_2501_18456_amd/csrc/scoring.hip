@@ -581,7 +581,7 @@ hipError_t launch_mutant_scan(const float* h, const float* J, const int8_t* wt, 
 // F_ij = F_ji = the square root.  Block-rows i and L - 1 - i share a run of
 // wave tasks (L - 1 blocks between them), so every run is as long.  J is read
 // once, without LDS staging.  k_apc_rows: S_i = sum_k F_ik (one wave per
-// row); k_apc_total: S = sum_i S_i; k_apc_out: F_apc = F - S_i S_j / S,
+// row); k_apc_out: S = sum_i S_i, F_apc = F - S_i S_j / S,
 // diagonals 0 (the diagonal of F is never read).
 // ---------------------------------------------------------------------------
 size_t apc_ws_bytes(int L) { return align256(sizeof(double) * ((size_t)L * L + L + 8)); }
@@ -701,9 +701,15 @@ __global__ __launch_bounds__(256) void k_apc_rows(const double* __restrict__ F, 
   if (lane == 0) S[i] = s;
 }
 
-// S = sum_i S_i: thread t adds S_t, S_{t+256}, ... in ascending order, then a
-// fixed tree over the 256 partial sums (one workgroup, deterministic).
-__global__ __launch_bounds__(256) void k_apc_total(double* __restrict__ S, int L) {
+// F_apc = F - S_i S_j / S.  Every workgroup adds S = sum_i S_i for itself (a few
+// loads; a launch of one workgroup for it took 4.7 us of 80 at L = 512): thread
+// t adds S_t, S_{t+256}, ... in ascending order, then a fixed tree over the 256
+// partial sums.
+constexpr int kApcPer = 4;  // entries per thread
+__global__ __launch_bounds__(256) void k_apc_out(const double* __restrict__ F,
+                                                 const double* __restrict__ S, int L,
+                                                 float* __restrict__ Fout,
+                                                 float* __restrict__ Fapc) {
   __shared__ double part[256];
   double tot = 0.0;
   for (int i = threadIdx.x; i < L; i += 256) tot += S[i];
@@ -713,17 +719,16 @@ __global__ __launch_bounds__(256) void k_apc_total(double* __restrict__ S, int L
     if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) S[L] = part[0];
-}
-
-__global__ void k_apc_out(const double* __restrict__ F, const double* __restrict__ S, int L,
-                          float* __restrict__ Fout, float* __restrict__ Fapc) {
-  const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= (size_t)L * L) return;
-  const int i = (int)(k / L), j = (int)(k % L);
-  const double f = (i == j) ? 0.0 : F[k];
-  if (Fout) Fout[k] = (float)f;
-  Fapc[k] = (i == j) ? 0.0f : (float)(f - S[i] * S[j] / S[L]);
+  const double all = part[0];
+#pragma unroll
+  for (int e = 0; e < kApcPer; ++e) {
+    const size_t k = ((size_t)blockIdx.x * kApcPer + e) * 256 + threadIdx.x;
+    if (k >= (size_t)L * L) return;
+    const int i = (int)(k / L), j = (int)(k % L);
+    const double f = (i == j) ? 0.0 : F[k];
+    if (Fout) Fout[k] = (float)f;
+    Fapc[k] = (i == j) ? 0.0f : (float)(f - S[i] * S[j] / all);
+  }
 }
 
 hipError_t launch_apc(const float* J, int L, int q, int gap, float* F, float* Fapc, void* ws,
@@ -744,9 +749,8 @@ hipError_t launch_apc(const float* J, int L, int q, int gap, float* F, float* Fa
       return hipErrorInvalidValue;
   }
   hipLaunchKernelGGL(k_apc_rows, dim3((unsigned)ceil_div(L, 4)), dim3(256), 0, s, Fd, L, S);
-  hipLaunchKernelGGL(k_apc_total, dim3(1), dim3(256), 0, s, S, L);
-  hipLaunchKernelGGL(k_apc_out, dim3((unsigned)ceil_div((size_t)L * L, (size_t)256)), dim3(256), 0,
-                     s, Fd, S, L, F, Fapc);
+  hipLaunchKernelGGL(k_apc_out, dim3((unsigned)ceil_div((int64_t)L * L, 256 * kApcPer)), dim3(256),
+                     0, s, Fd, S, L, F, Fapc);
   return hipGetLastError();
 }
 
