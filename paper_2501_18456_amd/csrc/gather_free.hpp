@@ -36,7 +36,9 @@ namespace bmdca {
 // every load count in the loader's wait (4% slower: the chains' waves wait
 // there), polls with a sleep between (2-6%), publishing a chunk later with more
 // in flight (5-15%), one loader (2-25%), three (even), twelve lanes per chain
-// of two states each (-7 to +20%), eight row reads ahead instead of six (even).
+// of two states each (-7 to +20%), one lane for both quads of a row of q = 5..8
+// (+3 to +30%), reads going on over the ends of groups and chunks (+30%), four
+// or eight row reads ahead instead of six (even).
 // Barriers -> free, ms, 256 CUs: q = 21, L = 100, 10 sweeps, 10 000 chains 5.22
 // -> 3.78; L = 256, 3 sweeps, 6000 chains 8.95 -> 5.71, 20 000 8.94 -> 7.6; L =
 // 512, 1 sweep, 10 000 11.7 -> 9.1, 20 000 24.4 -> 12.3; q = 25, L = 150, 3
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_free(
   const int cb = wid * CPW + gl / LPC;
   constexpr int nslot = 4;
   float* ring = reinterpret_cast<float*>(g_smem);                             // [nslot][slot]
-  uint32_t* tokw = reinterpret_cast<uint32_t*>(ring + (size_t)nslot * slot);  // [S][m4][CPB]
+  uint32_t* tokw = reinterpret_cast<uint32_t*>(ring + (size_t)nslot * slot);
   unsigned char* tokb = reinterpret_cast<unsigned char*>(tokw);
   const int64_t c =
       count ? (int64_t)cb * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * cpb + cb;
@@ -130,7 +132,8 @@ __global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_free(
   auto tok_off = [&](int j) -> uint32_t {
     const int m = j / S;
     if (TQ) return (uint32_t)((((j % S) * (m4 / 4) + (m >> 4)) * CPB + cb) * 16 + (m & 15));
-    return (uint32_t)((((j % S) * m4 + (m >> 2)) * CPB + cb) * 4 + (m & 3));
+    if (MH) return (uint32_t)((((j % S) * m4 + (m >> 2)) * CPB + cb) * 4 + (m & 3));
+    return (uint32_t)(((j % S) * CPB + cb) * m4 * 4 + m);
   };
   auto tok_at = [&](int j) -> unsigned char* { return tokb + tok_off(j); };
 
@@ -144,7 +147,9 @@ __global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_free(
       if (active && j < L) t = checked_token(chains[c * L + j], Q, dev_err);
       w |= (uint32_t)t << (8 * e);
     }
-    tokw[TQ ? ((uu * (m4 / 4) + (mq >> 2)) * CPB + cb) * 4 + (mq & 3) : k * CPB + cb] = w;
+    tokw[TQ   ? ((uu * (m4 / 4) + (mq >> 2)) * CPB + cb) * 4 + (mq & 3)
+         : MH ? k * CPB + cb
+              : (uu * CPB + cb) * m4 + mq] = w;
   }
 
   const uint32_t site_bytes = (uint32_t)((size_t)L * Q * QP * sizeof(float));
@@ -242,16 +247,15 @@ __global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_free(
   // positions starts with, read one step ahead (past the last: the last again)
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   const uint32_t twl = lds_addr(reinterpret_cast<const float*>(tokw)) +
-                       (TQ ? 16u : 4u) * (uint32_t)(u * (TQ ? m4 / 4 : m4) * CPB + cb);
+                       (TQ ? 16u * (uint32_t)(u * (m4 / 4) * CPB + cb)
+                           : 4u * (uint32_t)((u * CPB + cb) * m4));
   auto tokens = [&](int d0) -> u4 {
     if constexpr (TQ) {
       return *(__attribute__((address_space(3))) const u4*)(uintptr_t)(
           twl + (uint32_t)(d0 * CPB * 4));
     } else {
-      u4 t;
-#pragma unroll
-      for (int d = 0; d < 4; ++d) t[d] = lds_dword(twl + (uint32_t)(min(d0 + d, m4 - 1) * CPB * 4));
-      return t;
+      const uint32_t a = twl + 4u * (uint32_t)d0;
+      return u4{lds_dword(a), lds_dword(a + 4), lds_dword(a + 8), lds_dword(a + 12)};
     }
   };
   u4 g_tok = {0u, 0u, 0u, 0u};
@@ -480,7 +484,7 @@ __global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_free(
           const int mi = i / S;
 #pragma unroll
           for (int d = 0; d < 4; ++d)
-            if ((TQ ? d : min(d, m4 - 1)) == (mi >> 2))
+            if (d == (mi >> 2))
               g_tok[d] =
                   (g_tok[d] & ~(0xFFu << (8 * (mi & 3)))) | ((uint32_t)cnt << (8 * (mi & 3)));
         }
@@ -510,11 +514,18 @@ template <int Q, bool MH>
 hipError_t launch_free_shape(const GatherShape& gs, const GatherArgs& a) {
   constexpr int LP = gather_lanes(Q, !MH), LN = gather_narrow_lanes(Q, !MH);
   if (gs.ahead != 3 || gs.waves >= kGMaxWaves) return hipErrorInvalidValue;
-  // heat-bath chunks of whole groups of 16 positions: a lane's 16 tokens side
-  // by side, one 16-byte read
+  // Tokens of a heat-bath chain: in chunks of whole groups of 16 positions a
+  // lane's 16 tokens side by side, one 16-byte read; else all of a site group's
+  // side by side, an odd number of dwords apart from the next chain's.  Against
+  // dwords interleaved over the chains (four reads, each address clamped), as
+  // Metropolis has them: q = 5, L = 400, 10 000 chains, 5 sweeps 7.12 -> 6.74
+  // ms, q = 12, L = 200 3.65 -> 3.49, q = 25, L = 150, 3 sweeps 3.77 -> 3.46;
+  // Metropolis q = 21, L = 256 would take 3.9 ms for 3.6.
   const int S = gather_s(Q, gs.lpc), m4q = (int)gp_ceil(gs.m4, 4) * 4;
   const size_t grown = gs.lds + (size_t)S * (m4q - gs.m4) * 4 * (gs.waves * (64 / gs.lpc));
   const bool tq = !MH && gs.jc / S % 16 == 0 && grown <= kGLds;
+  const size_t odd = gs.lds + (size_t)S * 4 * (gs.waves * (64 / gs.lpc));
+  const int m4 = tq ? m4q : gs.m4 + (!MH && gs.m4 % 2 == 0 && odd <= kGLds ? 1 : 0);
   auto pick = [&](auto lanes) {
     constexpr int LL = decltype(lanes)::value;
     if constexpr (!MH) {
@@ -532,14 +543,14 @@ hipError_t launch_free_shape(const GatherShape& gs, const GatherArgs& a) {
     }
   }
   const int waves = std::min(gs.waves + kGLoaders, kGMaxWaves);
-  const size_t lds = (tq ? grown : gs.lds) + 4 * (kGMaxWaves + 1);
+  const size_t lds = (tq ? grown : m4 > gs.m4 ? odd : gs.lds) + 4 * (kGMaxWaves + 1);
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const DevCtl& ctl = *a.ctl;
   hipLaunchKernelGGL(kern, dim3(gs.blocks), dim3(waves * 64), lds, a.s, a.h, a.Jt, a.chains, a.N,
-                     a.L, gs.jc, gs.nchunk, tq ? m4q : gs.m4, gs.slot, gs.cpb, gs.waves, a.sweeps, (uint32_t)a.seed,
-                     (uint32_t)(a.seed >> 32), a.sweep_offset, a.beta, a.flips_out, a.dev_err,
+                     a.L, gs.jc, gs.nchunk, m4, gs.slot, gs.cpb, gs.waves, a.sweeps,
+                     (uint32_t)a.seed, (uint32_t)(a.seed >> 32), a.sweep_offset, a.beta, a.flips_out, a.dev_err,
                      ctl.epoch, ctl.active, ctl.streams, ctl.count);
   return hipGetLastError();
 }
