@@ -695,22 +695,47 @@ __global__ __launch_bounds__(256) void k_apc_rows(const double* __restrict__ F, 
   const int lane = threadIdx.x % 64;
   const int i = blockIdx.x * 4 + threadIdx.x / 64;
   if (i >= L) return;
+  // eight loads in flight, added in order (the diagonal and past the end: 0)
   double s = 0.0;
-  for (int k = lane; k < L; k += 64) s += (k == i) ? 0.0 : F[(size_t)i * L + k];
+  for (int k0 = 0; k0 < L; k0 += 512) {
+    double f[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + 64 * u + lane;
+      f[u] = k < L && k != i ? F[(size_t)i * L + k] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += f[u];
+  }
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
   if (lane == 0) S[i] = s;
 }
 
-// F_apc = F - S_i S_j / S.  Every workgroup adds S = sum_i S_i for itself (a few
-// loads; a launch of one workgroup for it took 4.7 us of 80 at L = 512): thread
-// t adds S_t, S_{t+256}, ... in ascending order, then a fixed tree over the 256
-// partial sums.
+// F_apc = F - S_i S_j / S.  Every workgroup adds S = sum_i S_i for itself while
+// its entries load: thread t adds S_t, S_{t+256}, ... in ascending order, then a
+// fixed tree over the 256 partial sums.  Latency bounds this and k_apc_rows
+// (eight loads in flight there): with a launch of one workgroup for S, one load
+// at a time and one entry per thread a call took 79.5 us at L = 512, q = 21, now
+// 76.3; 20.0 and 17.1 at L = 100.
 constexpr int kApcPer = 4;  // entries per thread
 __global__ __launch_bounds__(256) void k_apc_out(const double* __restrict__ F,
                                                  const double* __restrict__ S, int L,
                                                  float* __restrict__ Fout,
                                                  float* __restrict__ Fapc) {
   __shared__ double part[256];
+  const size_t n = (size_t)L * L;
+  // the entries and their rows' sums are on their way during the sum
+  double f[kApcPer], si[kApcPer], sj[kApcPer];
+  int row[kApcPer], col[kApcPer];
+#pragma unroll
+  for (int e = 0; e < kApcPer; ++e) {
+    const size_t k = min(((size_t)blockIdx.x * kApcPer + e) * 256 + threadIdx.x, n - 1);
+    row[e] = (int)(k / L);
+    col[e] = (int)(k % L);
+    f[e] = F[k];
+    si[e] = S[row[e]];
+    sj[e] = S[col[e]];
+  }
   double tot = 0.0;
   for (int i = threadIdx.x; i < L; i += 256) tot += S[i];
   part[threadIdx.x] = tot;
@@ -723,11 +748,9 @@ __global__ __launch_bounds__(256) void k_apc_out(const double* __restrict__ F,
 #pragma unroll
   for (int e = 0; e < kApcPer; ++e) {
     const size_t k = ((size_t)blockIdx.x * kApcPer + e) * 256 + threadIdx.x;
-    if (k >= (size_t)L * L) return;
-    const int i = (int)(k / L), j = (int)(k % L);
-    const double f = (i == j) ? 0.0 : F[k];
-    if (Fout) Fout[k] = (float)f;
-    Fapc[k] = (i == j) ? 0.0f : (float)(f - S[i] * S[j] / all);
+    if (k >= n) return;
+    if (Fout) Fout[k] = row[e] == col[e] ? 0.0f : (float)f[e];
+    Fapc[k] = row[e] == col[e] ? 0.0f : (float)(f[e] - si[e] * sj[e] / all);
   }
 }
 
