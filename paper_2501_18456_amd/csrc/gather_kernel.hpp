@@ -1,7 +1,8 @@
-// Gather-form sampler kernel (adabmDCA 2.0, Sec. 2.1): the heat-bath draw
-// and single-site Metropolis share the whole kernel but its draw step; the
-// two are instantiated in separate sources (sampler.hip, sampler_mh.hip) so
-// that they compile in parallel.
+// Gather-form sampler (adabmDCA 2.0, Sec. 2.1): its layout and draws, the kernel
+// whose waves keep step by barriers, and the choice among its forms.  The
+// heat-bath draw and single-site Metropolis share a kernel but for the draw
+// step; they are instantiated in separate sources (sampler.hip, sampler_mh.hip)
+// so that they compile in parallel.
 #pragma once
 #include <type_traits>
 
@@ -24,9 +25,9 @@ namespace bmdca {
 //     L*q*QP run, and the row a' = 0..QP-1 a chain needs is QP/4 16-byte
 //     quads.
 //   - Site i's run is streamed into LDS in chunks of JC sites by direct
-//     buffer->LDS loads, A = 3 chunks ahead of use, into a ring of A + 1
-//     slots.  JC is chosen per (L, q) to fill the LDS left over by the
-//     tokens.
+//     buffer->LDS loads into a ring of four slots, two chunks ahead of use here,
+//     up to three in the free-running form.  JC is chosen per (L, q) to fill the
+//     LDS left over by the tokens.
 //   - Each chain owns LPC = 8 or 16 consecutive lanes (16 for Metropolis at
 //     q <= 8; heat-bath chains with 5..7 quads per row may be narrow, one
 //     lane per quad, the lanes of the row group only), lane p = u * V + v

@@ -144,7 +144,9 @@ constexpr int gather_narrow_lanes(int q, bool small) {
   return (small && gather_v(q) == 8 && gather_qp(q) / 4 < 8) ? gather_qp(q) / 4 : 0;
 }
 
-// Paired chunk-steps: the ring of 4 slots is refilled two chunks at a time,
+// Paired chunk-steps (of the form with barriers, which plans of 16 waves run, all
+// of them paired by this rule; free-running waves have no steps to pair): the
+// ring of 4 slots is refilled two chunks at a time,
 // one wait and one barrier per two steps, with two chunks in flight instead
 // of three.  Where a workgroup holds at least this many chains the row
 // gathers dominate a step and the halved barriers pay (L = 256, q = 21,
@@ -160,9 +162,7 @@ constexpr int gather_narrow_lanes(int q, bool small) {
 // workgroup holds at least twice as many chains (10 000 chains, 40 per
 // workgroup: L = 400 (323 MB) 71.0 against 79.9 ms, L = 512 (528 MB) 115.3
 // against 130.3; L = 300 (181 MB) 41.0 against 40.6; L = 512, 20 000 chains,
-// 80 per workgroup: 254.9 against 246.2).  Launches on a share of the CUs
-// keep one barrier per step (the launch clears the flag).  The chains draw
-// the same bits either way.
+// 80 per workgroup: 254.9 against 246.2).  The chains draw the same bits either way.
 constexpr int kGPairChains = 32;
 constexpr double kGPairCacheBytes = 256.0 * 1024 * 1024;
 inline int gather_pair(int L, int q, int cpb) {
