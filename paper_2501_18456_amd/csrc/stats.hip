@@ -681,7 +681,10 @@ constexpr int kPCG = 4;
 // column); NC: copies of each histogram, lane group l / (64 / NC) of a wave
 // adding to copy l * NC / 64, summed when written out.  For q <= 8 a wave's
 // 64 increments fall on at most 64 bins and the same-bin adds serialize, so
-// 8 copies of 9 x 9 bins spread them.
+// 8 copies of 9 x 9 bins spread them, and a bin that several of a thread's four
+// chains share is added to once (conserved chains, q = 5, L = 400, 10 000: 438 ->
+// 295 us; at q = 21, L = 256, 20 000 conserved chains would take 400 us for 454,
+// uniform ones 267 for 243, so those add four times).
 template <int ROW, int NC>
 __global__ __launch_bounds__(256) void k_pair_counts(const int8_t* __restrict__ XT, int64_t Mpad,
                                                      int L, int q, double* __restrict__ C,
@@ -727,9 +730,19 @@ __global__ __launch_bounds__(256) void k_pair_counts(const int8_t* __restrict__ 
 #pragma unroll
       for (int g = 0; g < kPCG; ++g) {
         if (!on[g]) continue;  // uniform
+        uint32_t b[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          atomicAdd(&hist[g][ra[e] + min(__builtin_amdgcn_ubfe(wj[u][g], 8 * e, 8), kTrash)], 1u);
+          b[e] = ra[e] + min(__builtin_amdgcn_ubfe(wj[u][g], 8 * e, 8), kTrash);
+        if constexpr (NC > 1) {
+          atomicAdd(&hist[g][b[0]], 1u + (b[1] == b[0]) + (b[2] == b[0]) + (b[3] == b[0]));
+          if (b[1] != b[0]) atomicAdd(&hist[g][b[1]], 1u + (b[2] == b[1]) + (b[3] == b[1]));
+          if (b[2] != b[0] && b[2] != b[1]) atomicAdd(&hist[g][b[2]], 1u + (b[3] == b[2]));
+          if (b[3] != b[0] && b[3] != b[1] && b[3] != b[2]) atomicAdd(&hist[g][b[3]], 1u);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) atomicAdd(&hist[g][b[e]], 1u);
+        }
       }
     }
   }
