@@ -688,9 +688,15 @@ hipError_t launch_free_metropolis(int q, const GatherShape& gs, const GatherArgs
 // q = 12, L = 50, 6000 chains, 5 sweeps, 0.43 -> 0.33; q = 5, L = 400, 20 000
 // chains, 3 sweeps, 6.88 -> 6.58; 15 waves, one more loading: q = 16, L = 100,
 // 30 000 chains, 3 sweeps, 1.74 -> 1.37, q = 9, L = 60, 5 sweeps 0.89 -> 0.89,
-// Metropolis q = 21, L = 100, 10 sweeps 5.02 -> 4.38.
+// Metropolis q = 21, L = 100, 10 sweeps 5.02 -> 4.38.  The barriers also keep
+// Metropolis of q <= 4 on long models with many chains, whose steps are hundreds
+// of sites long: L = 511, 9000 chains, 3 sweeps, q = 3 10.5 -> 10.9, q = 4 11.0 ->
+// 11.4; L = 300 3.16 -> 3.13, q = 5 11.4 -> 11.2, 5000 chains 7.74 -> 7.36.
 constexpr int kGLoaders = 2;
-inline bool gather_free(const GatherShape& gs) { return gs.waves < kGMaxWaves; }
+inline bool gather_free(const GatherShape& gs, int L, int q, bool mh) {
+  if (mh && q <= 4 && L > 400 && gs.cpb >= kGPairChains) return false;
+  return gs.waves < kGMaxWaves;
+}
 
 // Sweeps of the gather form over the laid-out blocks Jt (q = 2..32).
 template <bool MH>
@@ -707,7 +713,7 @@ hipError_t launch_gather_form(const float* h, const float* Jt, int8_t* chains, i
   if (gs.waves == 0 || gs.ahead != 3) return hipErrorInvalidValue;
   const GatherArgs a{h, Jt, chains, N, L, sweeps, seed, sweep_offset, beta, flips_out, dev_err,
                      s, &ctl};
-  if (gather_free(gs))
+  if (gather_free(gs, L, q, MH))
     return MH        ? launch_free_metropolis(q, gs, a)
            : q <= 16 ? launch_free_heat(q, gs, a)
                      : launch_free_heat_wide(q, gs, a);

@@ -17,7 +17,8 @@ CHECKED = 48  # chains replayed by the oracle at each end of the launch
 # one chunk, two, three and many; whole and ragged last chunks (4, 8, 12 and 16
 # positions); chunks of 1 KB blocks that are no multiple of four; site groups 1,
 # 2, 4 and 8; 8, 16 and narrow lanes; 4 to 14 waves of chains with two loading,
-# 15 with one, 16 (the form with barriers); a workgroup of one chain
+# 15 with one, 16 (the form with barriers, as for Metropolis of q <= 4 past 400
+# sites); a workgroup of one chain
 @pytest.mark.parametrize("L,q,N,sampler", [
     (30, 21, 5000, "gather"), (40, 21, 6001, "gather"), (50, 21, 10000, "gather"),
     (60, 21, 30000, "gather"), (41, 32, 7000, "gather"), (49, 25, 12000, "gather"),
@@ -25,6 +26,7 @@ CHECKED = 48  # chains replayed by the oracle at each end of the launch
     (131, 9, 6000, "gather"), (400, 5, 6000, "gather"), (257, 8, 5000, "gather"),
     (12, 21, 6000, "gather"), (13, 4, 3000, "gather"), (60, 16, 30000, "gather"),
     (33, 12, 32768, "gather"), (24, 7, 32000, "metropolis-gather"),
+    (401, 4, 8200, "metropolis-gather"), (400, 4, 8200, "metropolis-gather"),
     (30, 21, 20000, "metropolis-gather"), (41, 21, 257, "metropolis-gather"),
     (60, 16, 20000, "metropolis-gather"), (257, 5, 3000, "metropolis-gather"),
     (45, 32, 9000, "metropolis-gather"), (97, 12, 30000, "metropolis-gather"),
