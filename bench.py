@@ -45,9 +45,9 @@ GATHER_TRAFFIC_SOURCES = ("paper_2501_18456_amd/csrc/gather_kernel.hpp",
                           "paper_2501_18456_amd/csrc/common.hpp")
 # workload -> bytes per launch: the gather kernel's 10-sweep launch and the
 # field kernel's 5-sweep launch of the precision form (L = 256, N = 20 000)
-GATHER_TRAFFIC = {"sha256": "6e43891342b19d2558b6b03d0016c4c6009e47f97f3cd79fd6103f12122d2941",
-                  "bytes": {"precision": 1.05827e10,           # 1.05775e10 read + 5.18e6 written
-                            "precision-fields": 1.98177e+12}}  # 1.45992e+12 read + 5.2185e+11
+GATHER_TRAFFIC = {"sha256": "3c482659c4ac98d49a2e726350f4bb1266cf3b65cc06db29ee0cfd5134c89a39",
+                  "bytes": {"precision": 1.25806e+10,           # 1.25754e+10 read + 5.18e6 written
+                            "precision-fields": 1.98288e12}}  # 1.46101e12 read + 5.2187e+11
 
 
 def sources_digest():
