@@ -343,12 +343,13 @@ template <bool FINE>
 __global__ __launch_bounds__(64 * kEGroups) void k_energy_finish(
     const float* __restrict__ h, const int8_t* __restrict__ XT, int64_t Bpad, int64_t B, int L,
     int q, int parts, const double* __restrict__ part, float* __restrict__ E,
-    const int64_t* __restrict__ count) {
+    const int64_t* __restrict__ count, int64_t b0) {
   if (count && *count < B) B = *count;
-  if ((int64_t)blockIdx.x * 64 >= B) return;  // whole workgroup, before the barrier
+  b0 += (int64_t)blockIdx.x * 64;
+  if (b0 >= B) return;  // whole workgroup, before the barrier
   __shared__ double sums[kEGroups][64];
   const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
-  const int64_t b = (int64_t)blockIdx.x * 64 + lane;  // below Bpad
+  const int64_t b = b0 + lane;  // below Bpad
   double acc = 0.0;
   // batches of 16 sites; past the group's last one that site again, not added
   const int i1 = L * (g + 1) / kEGroups;
@@ -428,9 +429,13 @@ hipError_t launch_energy(const float* h, const float* J, const int8_t* seqs, int
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(plan.split ? k_energy_finish<true> : k_energy_finish<false>,
-                     dim3((unsigned)ceil_div(B, 64)), dim3(64 * kEGroups), 0, s, h, XT, plan.Bpad, B,
-                     L, q, plan.parts, part, E, count);
+  // one launch per 2^22 workgroups (a grid dimension holds fewer than 2^32
+  // work-items: 2^29 sequences would pass it)
+  const int64_t chunk = (int64_t)64 << 22;
+  for (int64_t b0 = 0; b0 < B; b0 += chunk)
+    hipLaunchKernelGGL(plan.split ? k_energy_finish<true> : k_energy_finish<false>,
+                       dim3((unsigned)ceil_div(std::min(chunk, B - b0), 64)), dim3(64 * kEGroups), 0, s,
+                       h, XT, plan.Bpad, B, L, q, plan.parts, part, E, count, b0);
   return hipGetLastError();
 }
 
