@@ -15,6 +15,8 @@
 #include "common.hpp"
 #include "internal.hpp"
 
+#include <type_traits>
+
 namespace bmdca {
 
 constexpr int kRwThreads = 256;
@@ -139,6 +141,14 @@ __global__ void k_encode_rows(const int8_t* __restrict__ msa, int64_t M, int64_t
 // time grows by that); the rest is the maxima (17 operations per 1024
 // products), staging and barriers, which two or three workgroups per CU
 // overlap (with two buffers fewer fit a CU: 12-60% longer by L).
+//
+// Tiles compared by planes are bound by the vector operations, P + 1 a word.
+// What kept them from it, M = 100 000 rows of one close family, L = 100, q = 21,
+// ms: 7.65 with the rows loaded and counted tile by tile, 64 columns at a time
+// and a 64-bit compare a pair; 4.35 with rows and counts kept over a run, 256
+// columns, the next one read ahead and 32 bits; 4.15 with four rows a thread
+// where their planes leave room (L = 30 1.18 -> 1.06), 3.57 with a third
+// workgroup on the CU.  (Every pair by planes, without the matrix cores: 3.68.)
 typedef __attribute__((address_space(3))) void rw_lds_t;
 typedef int rw_i4 __attribute__((ext_vector_type(4)));
 typedef int rw_i8 __attribute__((ext_vector_type(8)));
@@ -149,15 +159,25 @@ __global__ __launch_bounds__(kRwThreads, 2) void k_count_similar(
     const uint32_t* __restrict__ planes, const uint4* __restrict__ codes, int64_t Mpad, int64_t M,
     int maxmis, float thr, int filter, int chunk, int32_t* __restrict__ n_sim) {
   constexpr int U = rw_units(W), UC = U / 2;
-  constexpr int R = (P * W <= 40) ? 2 : 1;  // rows per thread of the plane compare
-  constexpr int kCols = 64;                 // columns it stages at a time
+  // rows per thread of the plane compare: what its registers hold
+  constexpr int R = P * W <= 20 ? 4 : P * W <= 40 ? 2 : 1;
   constexpr int kCodes = U * kRwTile * 16;  // a tile's column codes
-  constexpr int kBuf = kCodes > kCols * P * W * 4 ? kCodes : kCols * P * W * 4;
-  __shared__ __attribute__((aligned(16))) unsigned char buf[kBuf];
-  constexpr int kList = 1536;  // pairs the list holds, 2% of a tile's
-  __shared__ uint2 list[kList];
+  // columns it stages at a time, each with its counts by the 4 / R waves of other
+  // rows: as many as fit where the codes were
+  constexpr int kColBytes = P * W * 4 + 4 / R * 4;
+  constexpr int kCols = kRwTile * kColBytes <= kCodes ? kRwTile : kRwTile / 2;
+  static_assert(kCols * kColBytes <= kCodes, "the plane compare's columns");
+  __shared__ __attribute__((aligned(16))) unsigned char buf[kCodes];
+  // The list, 2% of a tile's pairs: the row in its block-row; the column after the
+  // first of the tile `base` or, in the second block-row (kSecond), after its first
+  // from there on.  Four bytes a pair; at W = 4, the longest code, three, so that
+  // three workgroups fit a CU there too.
+  constexpr int kList = 1504, kSecond = 0x8000, kListTiles = kSecond / kRwTile;
+  constexpr bool kThree = W == 4;
+  __shared__ uint32_t list[kThree ? 1 : kList];
+  __shared__ uint8_t list_row[kThree ? kList : 1];
+  __shared__ uint16_t list_col[kThree ? kList : 1];
   __shared__ int nlist;
-  __shared__ int colcnt[kCols];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = (int)(Mpad / kRwTile);
@@ -180,88 +200,6 @@ __global__ __launch_bounds__(kRwThreads, 2) void k_count_similar(
     }
     return mis;
   };
-  // the list's pairs, one per lane (all threads; the list is complete)
-  auto flush = [&]() {
-    const int n = nlist;
-    for (int e = tid; e < n; e += kRwThreads) {
-      const uint2 mn = list[e];
-      if (mismatches(mn.x, mn.y) <= maxmis) {
-        atomicAdd(n_sim + mn.x, 1);
-        atomicAdd(n_sim + mn.y, 1);
-      }
-    }
-    __syncthreads();
-    if (tid == 0) nlist = 0;
-    __syncthreads();
-  };
-  // every pair of a tile by planes: R rows per thread in registers, kCols
-  // columns at a time in LDS (broadcast reads), with R = 2 half of them per
-  // pair of waves; rows counted in registers, columns by ballots
-  auto whole = [&](int64_t m0, int64_t n0) {
-    uint32_t* sh = reinterpret_cast<uint32_t*>(buf);
-    const int64_t row0 = m0 + (R == 2 ? tid & 127 : tid);
-    uint32_t mine[R][P][W];
-    int count[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int64_t m = row0 + 128 * r;
-      count[r] = 0;
-#pragma unroll
-      for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int w = 0; w < W; ++w)
-          mine[r][p][w] = (m < M) ? planes[((size_t)m * kMaxPlanes + p) * W + w] : 0u;
-    }
-    for (int b = 0; b < kRwTile; b += kCols) {
-      const int nload = (int)std::min<int64_t>(kCols, M - (n0 + b));
-      if (nload <= 0) break;  // uniform
-      __syncthreads();
-      for (int k = tid; k < nload * P * W; k += kRwThreads) {
-        const int nl = k / (P * W), pw = k % (P * W);
-        sh[k] = planes[(size_t)(n0 + b + nl) * kMaxPlanes * W + pw];
-      }
-      if (tid < kCols) colcnt[tid] = 0;
-      __syncthreads();
-      const int half = R == 2 ? wid >> 1 : 0;
-      const int nl1 = R == 2 ? min(nload, 32 * (half + 1)) : nload;
-      for (int nl = 32 * half; nl < nl1; ++nl) {
-        const uint32_t* o = sh + nl * P * W;
-        int mism[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) mism[r] = 0;
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-          uint32_t ow[P];
-#pragma unroll
-          for (int p = 0; p < P; ++p) ow[p] = o[p * W + w];
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            // d = OR_p (mine_p ^ other_p), one three-input bit operation per plane
-            uint32_t d = mine[r][0][w] ^ ow[0];
-#pragma unroll
-            for (int p = 1; p < P; ++p)
-              d = __builtin_amdgcn_bitop3_b32(mine[r][p][w], ow[p], d, kXorOr);
-            mism[r] += __popc(d);
-          }
-        }
-        int wc = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int64_t m = row0 + 128 * r;
-          const bool sim = m < M && mism[r] <= maxmis && m < n0 + b + nl;
-          count[r] += sim ? 1 : 0;
-          wc += __popcll(__ballot(sim));
-        }
-        if (lane == 0 && wc > 0) atomicAdd(&colcnt[nl], wc);
-      }
-      __syncthreads();
-      if (tid < nload && colcnt[tid] > 0) atomicAdd(n_sim + n0 + b + tid, colcnt[tid]);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (count[r] > 0) atomicAdd(n_sim + row0 + 128 * r, count[r]);
-  };
-
   // tile s of the run: block-row and block-column; false past the run's last
   auto tile = [&](int s, int& rb, int& st) {
     rb = p0;
@@ -270,6 +208,141 @@ __global__ __launch_bounds__(kRwThreads, 2) void k_count_similar(
     rb = S - 1 - p0;
     st = rb + s - (S - p0);
     return s < c1 && rb != p0;  // the middle block-row of an odd S has no partner
+  };
+  // the list's pairs, one per lane (all threads; the list is complete)
+  int base = c0;
+  // first listed column of the first and the second block-row
+  auto first_col = [&](bool second) -> int64_t {
+    const int st = second ? S - 1 - p0 + max(base - (S - p0), 0) : p0 + base;
+    return (int64_t)st * kRwTile;
+  };
+  auto flush = [&]() {
+    const int n = nlist;
+    const int64_t f0 = first_col(false), f1 = first_col(true);
+    for (int e = tid; e < n; e += kRwThreads) {
+      const int c = kThree ? list_col[e] : list[e] & 0xFFFF;
+      const int r = kThree ? list_row[e] : list[e] >> 16;
+      const int64_t m = (c & kSecond ? (int64_t)(S - 1 - p0) * kRwTile : (int64_t)p0 * kRwTile) + r;
+      const int64_t k = (c & kSecond ? f1 - kSecond : f0) + c;
+      if (mismatches(m, k) <= maxmis) {
+        atomicAdd(n_sim + m, 1);
+        atomicAdd(n_sim + k, 1);
+      }
+    }
+    __syncthreads();
+    if (tid == 0) nlist = 0;
+    __syncthreads();
+  };
+  // Every pair of the run's tiles from s on, by planes: R rows per thread in
+  // registers, loaded once per block-row; kCols columns at a time in LDS
+  // (broadcast reads; short ones are on their way while the column before is
+  // compared), an R-th of them per wave.  Rows are counted in registers, a wave's
+  // columns one per lane.  (A row past M has no column after it.)
+  auto by_planes = [&](int s) {
+    constexpr int PW = P * W, kWaveCols = kCols / R;  // columns per wave
+    uint32_t* sh = reinterpret_cast<uint32_t*>(buf);
+    int* colcnt = reinterpret_cast<int*>(sh + kCols * PW);
+    // rows r0 + kStep r of the tile, columns c0w .. of the staged ones
+    constexpr int kStep = kRwTile / R, kParts = 4 / R;
+    const int r0 = tid & (kStep - 1);
+    const int part = wid & (kParts - 1), c0w = wid / kParts * kWaveCols;
+    int rb, st;
+    bool more = tile(s, rb, st);
+    while (more) {
+      const int row = rb;
+      const int64_t m0 = (int64_t)rb * kRwTile;
+      uint32_t mine[R][PW];
+      int count[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int64_t m = m0 + r0 + kStep * r;
+        count[r] = 0;
+#pragma unroll
+        for (int k = 0; k < PW; ++k)
+          mine[r][k] = m < M ? planes[(size_t)m * kMaxPlanes * W + k] : 0u;
+      }
+      for (; more && rb == row; more = tile(++s, rb, st)) {
+        const int64_t n0 = (int64_t)st * kRwTile;
+        for (int b = 0; b < kRwTile; b += kCols) {
+          const int nload = (int)std::min<int64_t>(kCols, M - (n0 + b));
+          if (nload <= 0) break;  // uniform
+          __syncthreads();
+          for (int k = tid; k < nload * PW; k += kRwThreads) {
+            const int nl = k / PW, pw = k % PW;
+            sh[k] = planes[(size_t)(n0 + b + nl) * kMaxPlanes * W + pw];
+          }
+          __syncthreads();
+          // DIAG: the tile of the rows themselves, columns after the row only
+          auto compare = [&](auto diag) {
+            constexpr bool DIAG = decltype(diag)::value;
+            for (int g = c0w; g < c0w + kWaveCols; g += 64) {  // a column per lane
+              const int g1 = min(min(g + 64, c0w + kWaveCols), nload);
+              int mycol = 0;
+              auto column = [&](const uint32_t(&o)[PW], int nl) {
+                int wc = 0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                  int mism = 0;
+#pragma unroll
+                  for (int w = 0; w < W; ++w) {
+                    // d = OR_p (mine_p ^ other_p), one three-input bit operation per plane
+                    uint32_t d = mine[r][w] ^ o[w];
+#pragma unroll
+                    for (int p = 1; p < P; ++p)
+                      d = __builtin_amdgcn_bitop3_b32(mine[r][p * W + w], o[p * W + w], d, kXorOr);
+                    mism += __popc(d);
+                  }
+                  const bool sim = mism <= maxmis && (!DIAG || r0 + kStep * r < b + nl);
+                  count[r] += sim ? 1 : 0;
+                  wc += __popcll(__ballot(sim));
+                }
+                mycol = lane == nl - g ? wc : mycol;
+              };
+              auto read = [&](uint32_t(&o)[PW], int nl) {  // past the last: the last again
+                const uint32_t* src = sh + min(nl, g1 - 1) * PW;
+#pragma unroll
+                for (int k = 0; k < PW; ++k) o[k] = src[k];
+              };
+              if (g < g1) {
+                if constexpr (PW <= 20) {
+                  uint32_t x[PW], y[PW];
+                  read(x, g);
+                  int nl = g;
+                  for (; nl + 2 <= g1; nl += 2) {
+                    read(y, nl + 1);
+                    column(x, nl);
+                    read(x, nl + 2);
+                    column(y, nl + 1);
+                  }
+                  if (nl < g1) column(x, nl);
+                } else {
+                  for (int nl = g; nl < g1; ++nl) {
+                    uint32_t x[PW];
+                    read(x, nl);
+                    column(x, nl);
+                  }
+                }
+              }
+              if (g + lane < c0w + kWaveCols) colcnt[part * kCols + g + lane] = mycol;
+            }
+          };
+          if (st == row)
+            compare(std::true_type{});
+          else
+            compare(std::false_type{});
+          __syncthreads();
+          if (tid < nload) {
+            int c = 0;
+#pragma unroll
+            for (int k = 0; k < kParts; ++k) c += colcnt[k * kCols + tid];
+            if (c > 0) atomicAdd(n_sim + n0 + b + tid, c);
+          }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (count[r] > 0) atomicAdd(n_sim + m0 + r0 + kStep * r, count[r]);
+    }
   };
   rw_i4 a[2][UC];
   // block-column st's codes into LDS by direct loads
@@ -307,38 +380,51 @@ __global__ __launch_bounds__(kRwThreads, 2) void k_count_similar(
       }
     }
   };
-  auto open = [&](const rw_f16(&acc)[2]) {  // any pair of the wave's that thr leaves open
+  // any pair of the wave's that thr leaves open and the list may have room for (a
+  // tile with more will be done by planes)
+  float least = thr;
+  auto open = [&](const rw_f16(&acc)[2]) {
     float mx = acc[0][0];
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
       for (int v = 0; v < 16; ++v) mx = fmaxf(mx, acc[k][v]);
-    return __any(mx >= thr);
+    return __any(mx >= least);
   };
   // Appends the wave's open pairs of column block cb: a bit per product
   // (element e = 16 k + v of the lane at bit 31 - e), then one pair per lane
-  // and turn, with one LDS atomic per turn.
-  auto append = [&](const rw_f16(&acc)[2], int64_t m0, int64_t n0, int cb) {
+  // and turn, with one LDS atomic per turn; `col`: what the list has for the
+  // tile's first column.
+  auto append = [&](const rw_f16(&acc)[2], int64_t m0, int64_t n0, int col, int cb) {
     uint32_t mask = 0;
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
       for (int v = 0; v < 16; ++v) mask = mask + mask + (acc[k][v] >= thr ? 1u : 0u);
-    const uint32_t n = (uint32_t)n0 + 32 * cb + (lane & 31);
+    const int nt = 32 * cb + (lane & 31);  // column in the tile
+    int seen = 0;
     while (__any(mask != 0)) {
       const int e = mask ? __clz((int)mask) : 0;
       // product v: row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32
-      const uint32_t m = (uint32_t)m0 + 64 * wid + 32 * (e >> 4) + 8 * ((e >> 2) & 3) +
-                         4 * (lane >> 5) + (e & 3);
-      const bool ok = mask != 0 && m < n && n < M;
+      const int mt = 64 * wid + 32 * (e >> 4) + 8 * ((e >> 2) & 3) + 4 * (lane >> 5) + (e & 3);
+      const bool ok = mask != 0 && (uint32_t)m0 + mt < (uint32_t)n0 + nt && (uint32_t)n0 + nt < M;
       mask &= ~(0x80000000u >> e);
       const unsigned long long who = __ballot(ok);
       if (who == 0) continue;
       int at = 0;
       if (lane == 0) at = atomicAdd(&nlist, __popcll(who));
-      at = __builtin_amdgcn_readfirstlane(at) + __popcll(who & ((1ull << lane) - 1));
-      if (ok && at < kList) list[at] = make_uint2(m, n);
+      seen = at = __builtin_amdgcn_readfirstlane(at);
+      at += __popcll(who & ((1ull << lane) - 1));
+      if (ok && at < kList) {
+        if constexpr (kThree) {
+          list_row[at] = (uint8_t)mt;
+          list_col[at] = (uint16_t)(col + nt);
+        } else {
+          list[at] = (uint32_t)(mt << 16 | (col + nt));
+        }
+      }
     }
+    if (seen > kList) least = INFINITY;
   };
   // code tiles from s on; returns the tile to go on with by planes (c1: none)
   auto by_code = [&](int s) {
@@ -359,6 +445,8 @@ __global__ __launch_bounds__(kRwThreads, 2) void k_count_similar(
       // this wave's share of the tile's codes is in LDS; after the barrier all is
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
       __syncthreads();
+      const int col = (int)(n0 - first_col(rb != p0)) + (rb != p0 ? kSecond : 0);
+      least = thr;
       rw_i4 b0[UC], b1[UC];
       rw_f16 acc0[2], acc1[2];
       columns(b0, 0);
@@ -367,8 +455,8 @@ __global__ __launch_bounds__(kRwThreads, 2) void k_count_similar(
         products(b0, acc0);
         columns(b0, min(cb + 2, kRwTile / 32 - 1));
         products(b1, acc1);
-        if (open(acc0)) append(acc0, m0, n0, cb);
-        if (open(acc1)) append(acc1, m0, n0, cb + 1);
+        if (open(acc0)) append(acc0, m0, n0, col, cb);
+        if (open(acc1)) append(acc1, m0, n0, col, cb + 1);
       }
       __syncthreads();  // the buffer's readers, the list
       const int now = nlist;
@@ -379,17 +467,18 @@ __global__ __launch_bounds__(kRwThreads, 2) void k_count_similar(
         return s;
       }
       kept = now;
-      if (now > kList / 2) {
+      if (now > kList / 2 || s - base == kListTiles - 1) {
         __syncthreads();
         flush();
         kept = 0;
+        base = s + 1;
       }
       if (!tile(++s, rb, st)) return c1;
     }
   };
   __syncthreads();
   int s = filter ? by_code(c0) : c0;
-  for (int rb, st; tile(s, rb, st); ++s) whole((int64_t)rb * kRwTile, (int64_t)st * kRwTile);
+  by_planes(s);
   __syncthreads();
   flush();
 }
