@@ -508,28 +508,15 @@ __global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_free(
   }
 }
 
-// The loading waves come beside the plan's; the counters lie behind the
-// plan's LDS (kGLds leaves 256 bytes).
 template <int Q, bool MH>
 hipError_t launch_free_shape(const GatherShape& gs, const GatherArgs& a) {
   constexpr int LP = gather_lanes(Q, !MH), LN = gather_narrow_lanes(Q, !MH);
   if (gs.ahead != 3 || gs.waves >= kGMaxWaves) return hipErrorInvalidValue;
-  // Tokens of a heat-bath chain: in chunks of whole groups of 16 positions a
-  // lane's 16 tokens side by side, one 16-byte read; else all of a site group's
-  // side by side, an odd number of dwords apart from the next chain's.  Against
-  // dwords interleaved over the chains (four reads, each address clamped), as
-  // Metropolis has them: q = 5, L = 400, 10 000 chains, 5 sweeps 7.12 -> 6.74
-  // ms, q = 12, L = 200 3.65 -> 3.49, q = 25, L = 150, 3 sweeps 3.77 -> 3.46;
-  // Metropolis q = 21, L = 256 would take 3.9 ms for 3.6.
-  const int S = gather_s(Q, gs.lpc), m4q = (int)gp_ceil(gs.m4, 4) * 4;
-  const size_t grown = gs.lds + (size_t)S * (m4q - gs.m4) * 4 * (gs.waves * (64 / gs.lpc));
-  const bool tq = !MH && gs.jc / S % 16 == 0 && grown <= kGLds;
-  const size_t odd = gs.lds + (size_t)S * 4 * (gs.waves * (64 / gs.lpc));
-  const int m4 = tq ? m4q : gs.m4 + (!MH && gs.m4 % 2 == 0 && odd <= kGLds ? 1 : 0);
+  const FreeShape fs = free_shape(gs, Q, MH);
   auto pick = [&](auto lanes) {
     constexpr int LL = decltype(lanes)::value;
     if constexpr (!MH) {
-      if (tq) return k_gibbs_free<Q, LL, MH, true>;
+      if (fs.tq) return k_gibbs_free<Q, LL, MH, true>;
     }
     return k_gibbs_free<Q, LL, MH, false>;
   };
@@ -542,14 +529,12 @@ hipError_t launch_free_shape(const GatherShape& gs, const GatherArgs& a) {
       return hipErrorInvalidValue;
     }
   }
-  const int waves = std::min(gs.waves + kGLoaders, kGMaxWaves);
-  const size_t lds = (tq ? grown : m4 > gs.m4 ? odd : gs.lds) + 4 * (kGMaxWaves + 1);
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)fs.lds);
   if (e != hipSuccess) return e;
   const DevCtl& ctl = *a.ctl;
-  hipLaunchKernelGGL(kern, dim3(gs.blocks), dim3(waves * 64), lds, a.s, a.h, a.Jt, a.chains, a.N,
-                     a.L, gs.jc, gs.nchunk, m4, gs.slot, gs.cpb, gs.waves, a.sweeps,
+  hipLaunchKernelGGL(kern, dim3(gs.blocks), dim3(fs.waves * 64), fs.lds, a.s, a.h, a.Jt, a.chains, a.N,
+                     a.L, gs.jc, gs.nchunk, fs.m4, gs.slot, gs.cpb, fs.nw, a.sweeps,
                      (uint32_t)a.seed, (uint32_t)(a.seed >> 32), a.sweep_offset, a.beta, a.flips_out, a.dev_err,
                      ctl.epoch, ctl.active, ctl.streams, ctl.count);
   return hipGetLastError();

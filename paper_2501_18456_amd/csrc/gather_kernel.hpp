@@ -671,9 +671,7 @@ hipError_t launch_gather_switch(int q, const GatherShape& gs, const GatherArgs& 
 }
 
 // ----- sampler_few.hip: heat-bath sweeps of few chains, a workgroup per chain,
-// reading J itself; gather_few: whether N chains on `cus` CUs take it
-constexpr int64_t kGFewPerCu = 16;  // workgroups per CU counted on at most
-bool gather_few(int64_t N, int L, int q, int64_t cus);
+// reading J itself
 hipError_t launch_gather_few(int q, const float* J, const GatherArgs& a, int64_t cus);
 
 // ----- sampler_free.hip, sampler_free_wide.hip, sampler_free_mh.hip: sweeps
@@ -681,22 +679,6 @@ hipError_t launch_gather_few(int q, const float* J, const GatherArgs& a, int64_t
 hipError_t launch_free_heat(int q, const GatherShape& gs, const GatherArgs& a);
 hipError_t launch_free_heat_wide(int q, const GatherShape& gs, const GatherArgs& a);
 hipError_t launch_free_metropolis(int q, const GatherShape& gs, const GatherArgs& a);
-
-// Free-running waves wherever a wave is left to load: plans of 16 waves (more
-// than 120 chains per workgroup in 8 lanes, 60 in 16) keep the barriers, which
-// need no wave of their own.  Barriers -> free at either end of the range, ms:
-// q = 12, L = 50, 6000 chains, 5 sweeps, 0.43 -> 0.33; q = 5, L = 400, 20 000
-// chains, 3 sweeps, 6.88 -> 6.58; 15 waves, one more loading: q = 16, L = 100,
-// 30 000 chains, 3 sweeps, 1.74 -> 1.37, q = 9, L = 60, 5 sweeps 0.89 -> 0.89,
-// Metropolis q = 21, L = 100, 10 sweeps 5.02 -> 4.38.  The barriers also keep
-// Metropolis of q <= 4 on long models with many chains, whose steps are hundreds
-// of sites long: L = 511, 9000 chains, 3 sweeps, q = 3 10.5 -> 10.9, q = 4 11.0 ->
-// 11.4; L = 300 3.16 -> 3.13, q = 5 11.4 -> 11.2, 5000 chains 7.74 -> 7.36.
-constexpr int kGLoaders = 2;
-inline bool gather_free(const GatherShape& gs, int L, int q, bool mh) {
-  if (mh && q <= 4 && L > 400 && gs.cpb >= kGPairChains) return false;
-  return gs.waves < kGMaxWaves;
-}
 
 // Sweeps of the gather form over the laid-out blocks Jt (q = 2..32).
 template <bool MH>

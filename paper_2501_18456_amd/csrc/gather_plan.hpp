@@ -196,4 +196,102 @@ inline GatherShape gather_plan(int64_t N, int L, int q, int64_t cus, int cap = k
   return g;
 }
 
+// Free-running waves wherever a wave is left to load: plans of 16 waves (more
+// than 120 chains per workgroup in 8 lanes, 60 in 16) keep the barriers, which
+// need no wave of their own.  Barriers -> free at either end of the range, ms:
+// q = 12, L = 50, 6000 chains, 5 sweeps, 0.43 -> 0.33; q = 5, L = 400, 20 000
+// chains, 3 sweeps, 6.88 -> 6.58; 15 waves, one more loading: q = 16, L = 100,
+// 30 000 chains, 3 sweeps, 1.74 -> 1.37, q = 9, L = 60, 5 sweeps 0.89 -> 0.89,
+// Metropolis q = 21, L = 100, 10 sweeps 5.02 -> 4.38.  The barriers also keep
+// Metropolis of q <= 4 on long models with many chains, whose steps are hundreds
+// of sites long: L = 511, 9000 chains, 3 sweeps, q = 3 10.5 -> 10.9, q = 4 11.0 ->
+// 11.4; L = 300 3.16 -> 3.13, q = 5 11.4 -> 11.2, 5000 chains 7.74 -> 7.36.
+constexpr int kGLoaders = 2;
+inline bool gather_free(const GatherShape& gs, int L, int q, bool mh) {
+  if (mh && q <= 4 && L > 400 && gs.cpb >= kGPairChains) return false;
+  return gs.waves < kGMaxWaves;
+}
+
+// Waves, token layout and LDS of the free-running form of a plan.
+struct FreeShape {
+  int nw;      // waves that hold chains; the others load
+  int waves;   // waves per workgroup
+  bool tq;     // tokens of 16 positions side by side
+  int m4;      // token dwords per (chain, site group)
+  size_t lds;  // dynamic LDS bytes
+};
+
+// Tokens of a heat-bath chain: in chunks of whole groups of 16 positions a
+// lane's 16 tokens side by side, one 16-byte read; else all of a site group's
+// side by side, an odd number of dwords apart from the next chain's.  Against
+// dwords interleaved over the chains (four reads, each address clamped), as
+// Metropolis has them: q = 5, L = 400, 10 000 chains, 5 sweeps 7.12 -> 6.74
+// ms, q = 12, L = 200 3.65 -> 3.49, q = 25, L = 150, 3 sweeps 3.77 -> 3.46;
+// Metropolis q = 21, L = 256 would take 3.9 ms for 3.6.
+// The loading waves come beside the plan's; the counters (chunks consumed by
+// each wave, chunks complete) lie behind the tokens, kGLds leaves 256 bytes for
+// them.
+inline FreeShape free_shape(const GatherShape& gs, int q, bool mh) {
+  FreeShape f{};
+  const int S = gather_s(q, gs.lpc), m4q = (int)gp_ceil(gs.m4, 4) * 4;
+  const size_t col = (size_t)S * 4 * (gs.waves * (64 / gs.lpc));  // bytes of a token dword of all
+  f.nw = gs.waves;
+  f.waves = std::min(f.nw + kGLoaders, kGMaxWaves);
+  f.tq = !mh && gs.jc / S % 16 == 0 && gs.lds + (m4q - gs.m4) * col <= kGLds;
+  f.m4 = f.tq ? m4q : gs.m4 + (!mh && gs.m4 % 2 == 0 && gs.lds + col <= kGLds ? 1 : 0);
+  f.lds = gs.lds + (f.m4 - gs.m4) * col + 4 * (kGMaxWaves + 1);
+  return f;
+}
+
+// ---------------------------------------------------------------------------
+// A workgroup per chain (sampler_few.hip).
+// ---------------------------------------------------------------------------
+constexpr int64_t kGFewPerCu = 16;  // workgroups per CU counted on at most
+
+struct FewShape {
+  int waves;      // 2 or 3
+  int rowf;       // floats of a row buffer
+  size_t lds;     // dynamic LDS bytes
+  int64_t fits;   // workgroups per CU (0: the LDS does not hold one)
+};
+
+inline FewShape few_shape(int L, int q, int waves) {
+  const int qp = gather_qp(q), nq = qp / 4, S = gather_s(q, 8);
+  const int nit = (int)gp_ceil(L * nq, 64), nb = (int)gp_ceil(q * nq, 64);
+  const int lr = (int)gp_ceil(L, S) + 9;  // positions read, past the last one too
+  FewShape f{};
+  f.waves = waves;
+  f.rowf = std::max(nit * 256, lr * S * qp);
+  const size_t wavef = (size_t)f.rowf + (waves - 1) * nb * 256 + 96;
+  f.lds = sizeof(float) * (waves * wavef + nit * 64 + 4) + (size_t)gp_ceil(L, 16) * 16;
+  f.fits = std::min<int64_t>(kGFewPerCu, (int64_t)(kGLds / f.lds));
+  return f;
+}
+
+// Three waves for one or two chains per CU (L = 100, q = 21, 128 chains: 0.85
+// us a visit, 0.94 with two waves; 1024 chains 1.71 and 1.22), and where a CU
+// takes so few workgroups of two that the chains come in several rounds (L =
+// 400, 1024 chains: 7.8 and 9.0).
+inline FewShape few_plan(int64_t N, int L, int q, int64_t cus) {
+  const FewShape f3 = few_shape(L, q, 3), f2 = few_shape(L, q, 2);
+  if (N <= cus * std::min<int64_t>(2, f3.fits)) return f3;
+  return (f3.fits > 0 && f2.fits <= 3 && N > cus * f2.fits) ? f3 : f2;
+}
+
+// Chains per CU up to which a workgroup per chain is the faster form.  The
+// gather form's visit costs at least its staging, L q QP floats, whatever the
+// number of chains (up to 24 per CU); here it costs the chains' rows.  Measured,
+// us per visit, here and there: q = 21, L = 120: 2.2 and 3.9 with 1280 chains,
+// 3.6 and 3.9 with 2816, 4.5 and 3.9 with 3328; L = 300 (one workgroup per CU)
+// 7.3 and 8.9 with 1280, 10.2 and 8.9 with 1792; q = 12, L = 120: 1.8 and 2.4
+// with 2304, L = 300: 4.5 and 4.9 with 1792, 6.2 and 5.0 with 2304; q = 5, L =
+// 120: 0.9 and 1.2 with 1280, L = 300: 2.1 and 2.4 with 1280, 2.7 and 2.4 with
+// 1536; q = 32, L = 120: 5.5 and 6.1 with 3072, 8.1 and 6.2 with 4608.
+inline bool gather_few(int64_t N, int L, int q, int64_t cus) {
+  const FewShape f = few_plan(N, L, q, cus);
+  if (f.fits == 0) return false;
+  const int64_t most = q <= 8 ? 5 : q <= 16 ? 8 : q <= 24 ? 11 : 13;
+  return N <= cus * (f.fits > 1 ? most : most / 2 + 1);
+}
+
 }  // namespace bmdca

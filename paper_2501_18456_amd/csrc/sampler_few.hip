@@ -310,56 +310,6 @@ __global__ __launch_bounds__(64 * W) void k_gibbs_few(
   if (flips_out && lane == 0 && nflip) atomicAdd(flips_out, nflip);
 }
 
-namespace {
-
-struct FewShape {
-  int waves;      // 2 or 3
-  int rowf;       // floats of a row buffer
-  size_t lds;     // dynamic LDS bytes
-  int64_t fits;   // workgroups per CU (0: the LDS does not hold one)
-};
-
-FewShape few_shape(int L, int q, int waves) {
-  const int qp = gather_qp(q), nq = qp / 4, S = gather_s(q, 8);
-  const int nit = (int)ceil_div(L * nq, 64), nb = (int)ceil_div(q * nq, 64);
-  const int lr = (int)ceil_div(L, S) + 9;  // positions read, past the last one too
-  FewShape f{};
-  f.waves = waves;
-  f.rowf = std::max(nit * 256, lr * S * qp);
-  const size_t wavef = (size_t)f.rowf + (waves - 1) * nb * 256 + 96;
-  f.lds = sizeof(float) * (waves * wavef + nit * 64 + 4) + (size_t)ceil_div(L, 16) * 16;
-  f.fits = std::min<int64_t>(kGFewPerCu, (int64_t)(kGLds / f.lds));
-  return f;
-}
-
-// Three waves for one or two chains per CU (L = 100, q = 21, 128 chains: 0.85
-// us a visit, 0.94 with two waves; 1024 chains 1.71 and 1.22), and where a CU
-// takes so few workgroups of two that the chains come in several rounds (L =
-// 400, 1024 chains: 7.8 and 9.0).
-FewShape few_plan(int64_t N, int L, int q, int64_t cus) {
-  const FewShape f3 = few_shape(L, q, 3), f2 = few_shape(L, q, 2);
-  if (N <= cus * std::min<int64_t>(2, f3.fits)) return f3;
-  return (f3.fits > 0 && f2.fits <= 3 && N > cus * f2.fits) ? f3 : f2;
-}
-
-}  // namespace
-
-// Chains per CU up to which a workgroup per chain is the faster form.  The
-// gather form's visit costs at least its staging, L q QP floats, whatever the
-// number of chains (up to 24 per CU); here it costs the chains' rows.  Measured,
-// us per visit, here and there: q = 21, L = 120: 2.2 and 3.9 with 1280 chains,
-// 3.6 and 3.9 with 2816, 4.5 and 3.9 with 3328; L = 300 (one workgroup per CU)
-// 7.3 and 8.9 with 1280, 10.2 and 8.9 with 1792; q = 12, L = 120: 1.8 and 2.4
-// with 2304, L = 300: 4.5 and 4.9 with 1792, 6.2 and 5.0 with 2304; q = 5, L =
-// 120: 0.9 and 1.2 with 1280, L = 300: 2.1 and 2.4 with 1280, 2.7 and 2.4 with
-// 1536; q = 32, L = 120: 5.5 and 6.1 with 3072, 8.1 and 6.2 with 4608.
-bool gather_few(int64_t N, int L, int q, int64_t cus) {
-  const FewShape f = few_plan(N, L, q, cus);
-  if (f.fits == 0) return false;
-  const int64_t most = q <= 8 ? 5 : q <= 16 ? 8 : q <= 24 ? 11 : 13;
-  return N <= cus * (f.fits > 1 ? most : most / 2 + 1);
-}
-
 template <int Q, int W>
 static hipError_t launch_few_qw(const float* J, const GatherArgs& a, const FewShape& f) {
   auto kern = k_gibbs_few<Q, W>;
