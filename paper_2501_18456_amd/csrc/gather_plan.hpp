@@ -287,9 +287,16 @@ inline FewShape few_plan(int64_t N, int L, int q, int64_t cus) {
 // with 2304, L = 300: 4.5 and 4.9 with 1792, 6.2 and 5.0 with 2304; q = 5, L =
 // 120: 0.9 and 1.2 with 1280, L = 300: 2.1 and 2.4 with 1280, 2.7 and 2.4 with
 // 1536; q = 32, L = 120: 5.5 and 6.1 with 3072, 8.1 and 6.2 with 4608.
+// Of q <= 4 the staging is cheap (16 bytes a site and state) and the chains' rows
+// grow with L, so the line falls with it, from 5 chains per CU at 200 sites to 3
+// at 512; us a sweep here and there, q = 2: L = 200 200 and 220 with 1280, L = 230
+// 232 and 253 with 1030, 286 and 253 with 1280, L = 300 384 and 399 with 1024, 458
+// and 398 with 1030, L = 400 595 and 638 with 770, 693 and 640 with 1024, L = 512
+// 829 and 877 with 768, 1003 and 877 with 900.
 inline bool gather_few(int64_t N, int L, int q, int64_t cus) {
   const FewShape f = few_plan(N, L, q, cus);
   if (f.fits == 0) return false;
+  if (q <= 4 && 5 * N * L > cus * (8 * L + 3600)) return false;
   const int64_t most = q <= 8 ? 5 : q <= 16 ? 8 : q <= 24 ? 11 : 13;
   return N <= cus * (f.fits > 1 ? most : most / 2 + 1);
 }

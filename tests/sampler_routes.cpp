@@ -1,0 +1,32 @@
+// CPU check of the sampler's dispatch at shapes where both sides of a line were
+// measured: the form that a call takes, and the waves it runs.
+#include <cstdio>
+
+#include "../paper_2501_18456_amd/csrc/gather_plan.hpp"
+
+using namespace bmdca;
+
+static int failures = 0;
+#define CHECK(cond)                               \
+  do {                                            \
+    if (!(cond)) {                                \
+      std::printf("FAIL line %d: %s\n", __LINE__, #cond); \
+      ++failures;                                 \
+    }                                             \
+  } while (0)
+
+int main() {
+  // heat-bath, few chains on 256 CUs: a workgroup per chain or the staged form
+  auto few = [](int64_t N, int L, int q) { return gather_few(N, L, q, 256); };
+  for (int q : {2, 3, 4}) {
+    CHECK(few(1280, 200, q) && !few(1281, 200, q));
+    CHECK(few(1030, 230, q) && !few(1280, 230, q));
+    CHECK(few(1024, 300, q) && !few(1030, 300, q));
+    CHECK(few(770, 400, q) && !few(1024, 400, q));
+    CHECK(few(768, 512, q) && !few(900, 512, q) && !few(1280, 512, q));
+  }
+  CHECK(few(1280, 512, 5) && few(1280, 300, 8) && !few(1281, 300, 8));
+  CHECK(few(2816, 120, 21) && !few(2817, 120, 21));
+  std::printf("%d failures\n", failures);
+  return failures == 0 ? 0 : 1;
+}
