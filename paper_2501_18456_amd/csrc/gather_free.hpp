@@ -73,8 +73,15 @@ __device__ __forceinline__ void unroll_n(F&& f) {
   }
 }
 
+// Metropolis of q <= 8 runs two workgroups per CU where the chains take several
+// rounds (at most 60 chains and 15 to 16 waves each), if its registers allow 8
+// waves a SIMD: q = 4 and 8 took a few more than the 64 by themselves (q = 4, L =
+// 120, 25 000 chains, 3 sweeps 1.56 -> 1.32 ms; bound to 64, q = 5 would take 6%
+// longer).
+constexpr int free_simd_waves(int Q, bool mh) { return mh && (Q == 4 || Q == 8) ? 8 : 4; }
+
 template <int Q, int LPC, bool MH, bool TQ>
-__global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_free(
+__global__ __launch_bounds__(kGMaxWaves * 64, free_simd_waves(Q, MH)) void k_gibbs_free(
     const float* __restrict__ h, const float* __restrict__ Jt, int8_t* __restrict__ chains,
     int64_t N, int L, int jc, int nchunk, int m4, int slot, int cpb, int nw,
     int sweeps, uint32_t k0, uint32_t k1, uint64_t sweep_offset, float beta,

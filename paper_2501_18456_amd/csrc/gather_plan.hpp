@@ -202,15 +202,9 @@ inline GatherShape gather_plan(int64_t N, int L, int q, int64_t cus, int cap = k
 // q = 12, L = 50, 6000 chains, 5 sweeps, 0.43 -> 0.33; q = 5, L = 400, 20 000
 // chains, 3 sweeps, 6.88 -> 6.58; 15 waves, one more loading: q = 16, L = 100,
 // 30 000 chains, 3 sweeps, 1.74 -> 1.37, q = 9, L = 60, 5 sweeps 0.89 -> 0.89,
-// Metropolis q = 21, L = 100, 10 sweeps 5.02 -> 4.38.  The barriers also keep
-// Metropolis of q <= 4 on long models with many chains, whose steps are hundreds
-// of sites long: L = 511, 9000 chains, 3 sweeps, q = 3 10.5 -> 10.9, q = 4 11.0 ->
-// 11.4; L = 300 3.16 -> 3.13, q = 5 11.4 -> 11.2, 5000 chains 7.74 -> 7.36.
+// Metropolis q = 21, L = 100, 10 sweeps 5.02 -> 4.38.
 constexpr int kGLoaders = 2;
-inline bool gather_free(const GatherShape& gs, int L, int q, bool mh) {
-  if (mh && q <= 4 && L > 400 && gs.cpb >= kGPairChains) return false;
-  return gs.waves < kGMaxWaves;
-}
+inline bool gather_free(const GatherShape& gs) { return gs.waves < kGMaxWaves; }
 
 // Waves, token layout and LDS of the free-running form of a plan.
 struct FreeShape {
@@ -227,7 +221,17 @@ struct FreeShape {
 // dwords interleaved over the chains (four reads, each address clamped), as
 // Metropolis has them: q = 5, L = 400, 10 000 chains, 5 sweeps 7.12 -> 6.74
 // ms, q = 12, L = 200 3.65 -> 3.49, q = 25, L = 150, 3 sweeps 3.77 -> 3.46;
-// Metropolis q = 21, L = 256 would take 3.9 ms for 3.6.
+// Metropolis q = 21, L = 256 would take 3.9 ms for 3.6.  Interleaved dwords of a
+// chain of 16 lanes (16 or 8 site groups) are an odd number of rows of chains
+// apart too: with 4 or 8 the lanes of a chain read few banks (q = 2, L = 512, 1000
+// chains, one sweep 2.01 ms, 1.74 with the next rule, 1.54 with both).
+//
+// Waves: a plan has at least four, for the loads, but here a chains' wave without
+// chains only polls and reads LDS beside those that have some.  Chains of 16 lanes
+// take what holds them, and three for two waves' chains (even or up to 5% faster
+// than two): q = 8, L = 250, one sweep, 358 chains 680 -> 519 us, 2048 643 -> 581.
+// (In 8 lanes 0.86 to 1.05 of the time, and heat-bath sweeps of few chains have a
+// form of their own.)
 // The loading waves come beside the plan's; the counters (chunks consumed by
 // each wave, chunks complete) lie behind the tokens, kGLds leaves 256 bytes for
 // them.
@@ -235,10 +239,12 @@ inline FreeShape free_shape(const GatherShape& gs, int q, bool mh) {
   FreeShape f{};
   const int S = gather_s(q, gs.lpc), m4q = (int)gp_ceil(gs.m4, 4) * 4;
   const size_t col = (size_t)S * 4 * (gs.waves * (64 / gs.lpc));  // bytes of a token dword of all
-  f.nw = gs.waves;
+  const int need = (int)gp_ceil(gs.cpb, 64 / gs.lpc);
+  f.nw = gs.lpc != 16 ? gs.waves : need == 2 ? 3 : need;
   f.waves = std::min(f.nw + kGLoaders, kGMaxWaves);
   f.tq = !mh && gs.jc / S % 16 == 0 && gs.lds + (m4q - gs.m4) * col <= kGLds;
-  f.m4 = f.tq ? m4q : gs.m4 + (!mh && gs.m4 % 2 == 0 && gs.lds + col <= kGLds ? 1 : 0);
+  const bool odd = (!mh || gs.lpc == 16) && gs.m4 % 2 == 0 && gs.lds + col <= kGLds;
+  f.m4 = f.tq ? m4q : gs.m4 + (odd ? 1 : 0);
   f.lds = gs.lds + (f.m4 - gs.m4) * col + 4 * (kGMaxWaves + 1);
   return f;
 }

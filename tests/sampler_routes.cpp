@@ -27,6 +27,16 @@ int main() {
   }
   CHECK(few(1280, 512, 5) && few(1280, 300, 8) && !few(1281, 300, 8));
   CHECK(few(2816, 120, 21) && !few(2817, 120, 21));
+  // Metropolis by free-running waves: the waves that hold chains, and token rows
+  // of chains of 16 lanes an odd number apart
+  auto mh = [](int64_t N, int L, int q) {
+    const GatherShape g = gather_plan(N, L, q, 256, 128, false);
+    return gather_free(g) ? free_shape(g, q, true) : FreeShape{};
+  };
+  CHECK(mh(358, 512, 4).nw == 1 && mh(1024, 250, 8).nw == 1 && mh(2048, 250, 8).nw == 3);
+  CHECK(mh(2500, 250, 8).nw == 3 && mh(4096, 250, 8).nw == 4);
+  CHECK(mh(9000, 511, 3).nw == 9 && mh(9000, 511, 3).m4 % 2 == 1);
+  for (int L : {250, 323, 512}) CHECK(mh(358, L, 2).m4 % 2 == 1 && mh(358, L, 8).m4 % 2 == 1);
   std::printf("%d failures\n", failures);
   return failures == 0 ? 0 : 1;
 }
