@@ -695,7 +695,7 @@ hipError_t launch_gather_form(const float* h, const float* Jt, int8_t* chains, i
   if (gs.waves == 0 || gs.ahead != 3) return hipErrorInvalidValue;
   const GatherArgs a{h, Jt, chains, N, L, sweeps, seed, sweep_offset, beta, flips_out, dev_err,
                      s, &ctl};
-  if (gather_free(gs))
+  if (gather_free(gs, q, MH))
     return MH        ? launch_free_metropolis(q, gs, a)
            : q <= 16 ? launch_free_heat(q, gs, a)
                      : launch_free_heat_wide(q, gs, a);

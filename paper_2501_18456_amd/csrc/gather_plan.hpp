@@ -203,8 +203,24 @@ inline GatherShape gather_plan(int64_t N, int L, int q, int64_t cus, int cap = k
 // chains, 3 sweeps, 6.88 -> 6.58; 15 waves, one more loading: q = 16, L = 100,
 // 30 000 chains, 3 sweeps, 1.74 -> 1.37, q = 9, L = 60, 5 sweeps 0.89 -> 0.89,
 // Metropolis q = 21, L = 100, 10 sweeps 5.02 -> 4.38.
+// The barriers also keep heat-bath plans of many waves and 3 to 12 states whose
+// sites are one chunk each of other than whole groups of 16 positions a lane (the
+// free form reads their tokens by single dwords): from 9 waves on of q <= 4 and 20
+// positions, 12 of q <= 8, else 13.  Barriers and free there, ms, 3 sweeps: q = 4,
+// L = 200, 13 waves 1.34 and 1.54, 9 waves 1.10 and 1.18, L = 80, 14 waves 0.37 and
+// 0.40, q = 8, L = 70, 12 waves 0.40 and 0.43; with fewer waves, fewer positions or
+// whole groups the free form is even or faster (q = 4, L = 200, 8 waves 1.05 and
+// 0.95, L = 120, 13 waves 0.61 and 0.62, 12 waves 0.55 and 0.52).  Over 3250 shapes
+// of 7 to 15 waves a call takes at most 6% longer than by barriers, 0.90 of their
+// time in the mean.
 constexpr int kGLoaders = 2;
-inline bool gather_free(const GatherShape& gs) { return gs.waves < kGMaxWaves; }
+inline bool gather_free(const GatherShape& gs, int q, bool mh) {
+  const int positions = gs.jc / gather_s(q, gs.lpc);
+  if (!mh && q >= 3 && q <= 12 && gs.nchunk == 1 && positions >= 12 && positions % 16 != 0 &&
+      gs.waves >= (q <= 4 && positions >= 20 ? 9 : q <= 8 ? 12 : 13))
+    return false;
+  return gs.waves < kGMaxWaves;
+}
 
 // Waves, token layout and LDS of the free-running form of a plan.
 struct FreeShape {

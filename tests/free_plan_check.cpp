@@ -162,7 +162,7 @@ int main() {
           for (int cap : {128, kGShareChains})
             for (bool mh : {false, true}) {
               const GatherShape g = gather_plan(n, L, q, c, cap, !mh);
-              if (!gather_free(g)) continue;
+              if (!gather_free(g, q, mh)) continue;
               check_free(n, L, q, g, mh);
               ++shapes;
             }

@@ -31,12 +31,22 @@ int main() {
   // of chains of 16 lanes an odd number apart
   auto mh = [](int64_t N, int L, int q) {
     const GatherShape g = gather_plan(N, L, q, 256, 128, false);
-    return gather_free(g) ? free_shape(g, q, true) : FreeShape{};
+    return gather_free(g, q, true) ? free_shape(g, q, true) : FreeShape{};
   };
   CHECK(mh(358, 512, 4).nw == 1 && mh(1024, 250, 8).nw == 1 && mh(2048, 250, 8).nw == 3);
   CHECK(mh(2500, 250, 8).nw == 3 && mh(4096, 250, 8).nw == 4);
   CHECK(mh(9000, 511, 3).nw == 9 && mh(9000, 511, 3).m4 % 2 == 1);
   for (int L : {250, 323, 512}) CHECK(mh(358, L, 2).m4 % 2 == 1 && mh(358, L, 8).m4 % 2 == 1);
+  // heat-bath, many waves: barriers or free-running waves
+  auto free = [](int waves, int L, int q) {
+    const GatherShape g = gather_plan(256 * 8 * waves, L, q, 256);
+    CHECK(g.waves == waves);
+    return gather_free(g, q, false);
+  };
+  CHECK(!free(9, 200, 4) && !free(13, 150, 3) && free(8, 200, 4) && free(9, 80, 4));
+  CHECK(!free(14, 80, 4) && free(13, 120, 4) && free(13, 60, 4) && free(13, 200, 2));
+  CHECK(!free(12, 70, 8) && free(11, 70, 8) && !free(13, 100, 5) && free(13, 250, 5));
+  CHECK(!free(13, 50, 9) && free(12, 50, 9) && free(13, 80, 9) && free(13, 50, 16));
   std::printf("%d failures\n", failures);
   return failures == 0 ? 0 : 1;
 }
