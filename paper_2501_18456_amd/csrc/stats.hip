@@ -676,16 +676,19 @@ hipError_t launch_reduce_partials(const StatsPlan& plan, const void* ws, int Lq,
 // low 6 bits, without the clamps, ran 1.2-2.1x longer).
 // ---------------------------------------------------------------------------
 constexpr int kPCG = 4;
+constexpr int kPCMerge = 32;  // sites up to which every chain adds for itself
 
 // ROW: bins per histogram row (tokens clamped to ROW - 1, the trash row and
 // column); NC: copies of each histogram, lane group l / (64 / NC) of a wave
 // adding to copy l * NC / 64, summed when written out.  For q <= 8 a wave's
 // 64 increments fall on at most 64 bins and the same-bin adds serialize, so
-// 8 copies of 9 x 9 bins spread them, and a bin that several of a thread's four
-// chains share is added to once (conserved chains, q = 5, L = 400, 10 000: 438 ->
-// 295 us; at q = 21, L = 256, 20 000 conserved chains would take 400 us for 454,
-// uniform ones 267 for 243, so those add four times).
-template <int ROW, int NC>
+// 8 copies of 9 x 9 bins spread them, and with MERGE a bin that several of a
+// thread's four chains share is added to once (conserved chains, q = 5, L = 400,
+// 10 000: 438 -> 295 us; at q = 21, L = 256, 20 000 conserved chains would take 400
+// us for 454, uniform ones 267 for 243, so those add four times).  Up to 32 sites
+// (144 workgroups) a thread's own instructions bound the count, not the adds: q =
+// 5, L = 20, 37 000 chains, uniform 25 us without and 37 with it, conserved even.
+template <int ROW, int NC, bool MERGE>
 __global__ __launch_bounds__(256) void k_pair_counts(const int8_t* __restrict__ XT, int64_t Mpad,
                                                      int L, int q, double* __restrict__ C,
                                                      const int32_t* __restrict__ active) {
@@ -734,7 +737,7 @@ __global__ __launch_bounds__(256) void k_pair_counts(const int8_t* __restrict__ 
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           b[e] = ra[e] + min(__builtin_amdgcn_ubfe(wj[u][g], 8 * e, 8), kTrash);
-        if constexpr (NC > 1) {
+        if constexpr (MERGE) {
           atomicAdd(&hist[g][b[0]], 1u + (b[1] == b[0]) + (b[2] == b[0]) + (b[3] == b[0]));
           if (b[1] != b[0]) atomicAdd(&hist[g][b[1]], 1u + (b[2] == b[1]) + (b[3] == b[1]));
           if (b[2] != b[0] && b[2] != b[1]) atomicAdd(&hist[g][b[2]], 1u + (b[3] == b[2]));
@@ -779,9 +782,10 @@ hipError_t launch_pair_counts(const int8_t* X, int64_t N, int L, int q, const St
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)ceil_div(L, kPCG), (unsigned)L);
   if (q <= 8)
-    hipLaunchKernelGGL((k_pair_counts<9, 8>), grid, dim3(256), 0, s, XT, plan.Mpad, L, q, C, active);
+    hipLaunchKernelGGL((L > kPCMerge ? k_pair_counts<9, 8, true> : k_pair_counts<9, 8, false>), grid,
+                       dim3(256), 0, s, XT, plan.Mpad, L, q, C, active);
   else
-    hipLaunchKernelGGL((k_pair_counts<33, 1>), grid, dim3(256), 0, s, XT, plan.Mpad, L, q, C,
+    hipLaunchKernelGGL((k_pair_counts<33, 1, false>), grid, dim3(256), 0, s, XT, plan.Mpad, L, q, C,
                        active);
   return hipGetLastError();
 }
