@@ -452,16 +452,26 @@ hipError_t launch_energy(const float* h, const float* J, const int8_t* seqs, int
 //   wild type at L = 256, q = 21 took 21.7 + 4.1 us, now 7.1; 16 at L = 512 whole
 //   calls 65 -> 30 us.
 //   Otherwise a wave per (block, wild type), four wild types per workgroup.
-// With kMSplit workgroups or more, or eighths of few rows, the split form's row
-// addresses and exchange cost more than its latency saves: L = 512, 64 wild
-// types (2752) 102 us split, 78 not; L = 100, 150 (1350) 22.5 and 18; L = 256,
-// 64 (1408) 34.7 and 34.8.  Then, ROWS = 8 in flight while there are few waves
-// and many rows (L = 512, 64: 78 us, with four 83), else four (L = 100, 1000:
-// 49 us, with eight 67).
+// Which, by the number of (block, wild type) pairs, and ROWS, the rows in flight;
+// us, all rows of a wild type in one workgroup and the differences in a launch of
+// their own, then now:
+//   - up to 256 pairs, one a CU: split, 16 rows (latency), 23 -> 11 (L = 256, q = 21,
+//     one wild type);
+//   - while an eighth's rows are worth a wave, up to 64 L pairs, and up to 8192,
+//     where whole wild types fill the device: split, 2 rows (few registers: 32 waves
+//     a CU; with 16 rows 2 to 4 times longer), L = 180, q = 21, 100 wild types 28.6 ->
+//     20.0, L = 256, q = 3, 1000 35.4 -> 36.1, with 16 rows 80;
+//   - of more than 4096 fields the couplings no longer stay in the caches, and from
+//     2048 pairs on eight waves that read eight rows far apart cost more than they
+//     cover: whole wild types, 4 rows, L = 256, q = 21, 150 47.5 -> 49.9 (split 55), L
+//     = 500, 100 173 -> 156;
+//   - the rest whole, 2 rows, L = 40, q = 21, 4000 39 -> 38 (4 rows 52), L = 256, 1000
+//     431 -> 220; but 4 rows between 8192 waves, where 2 need a second round, and
+//     12 288 (L = 256, q = 21, 400 155 -> 99, 2 rows 128).
+// Over 929 sizes at most 1.12 of the two launches' time, 0.6 in the mean.
 // The sums are the same, so dE does not depend on the batch.
 // ---------------------------------------------------------------------------
 constexpr int kMParts = 8;
-constexpr int64_t kMSplit = 1536;
 template <bool SPLIT, int ROWS>
 __global__ __launch_bounds__(SPLIT ? 64 * kMParts : 256) void k_mutant_scan(
     const float* __restrict__ h, const float* __restrict__ J, const int8_t* __restrict__ wt,
@@ -561,10 +571,13 @@ hipError_t launch_mutant_scan(const float* h, const float* J, const int8_t* wt, 
   // blocks of equal width, so that every XCD's range holds the same work
   const int sites = (int)ceil_div(L, ceil_div(L, 256 / q));
   const int64_t blocks = ceil_div(L, sites);
-  const bool split = B * blocks <= std::min<int64_t>(kMSplit, 6 * L);
-  auto kern = split                            ? k_mutant_scan<true, 16>
-              : B * blocks <= 4096 && L >= 200 ? k_mutant_scan<false, 8>
-                                               : k_mutant_scan<false, 4>;
+  const int64_t pairs = B * blocks;
+  const bool large = L * q > 4096;
+  const bool split = pairs <= std::min<int64_t>(64 * L, large ? 2048 : 8192);
+  const bool four = (large && pairs <= 4800) || (L * q > 1600 && pairs > 8192 && pairs <= 12288);
+  auto kern = split  ? (pairs <= 256 ? k_mutant_scan<true, 16> : k_mutant_scan<true, 2>)
+              : four ? k_mutant_scan<false, 4>
+                     : k_mutant_scan<false, 2>;
   // one launch per 2^22 workgroups (a grid dimension holds fewer than 2^32 work-items)
   const int64_t nwg = ceil_div(B, split ? 1 : 4) * blocks, chunk = (int64_t)1 << 22;
   for (int64_t g0 = 0; g0 < nwg; g0 += chunk)
