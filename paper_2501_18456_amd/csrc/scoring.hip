@@ -14,8 +14,8 @@ namespace bmdca {
 //
 // The pairs i < j are walked as steps (column chunk jc of kEJC sites, row
 // site i), jc outer: a step needs the q x (kEJC*q) tile of J with rows
-// (i, a) and columns (j, b), j in the chunk.  A workgroup owns 2048 (q > 8)
-// or 1024 sequences (four per thread) and one contiguous range of steps; it stages
+// (i, a) and columns (j, b), j in the chunk.  A workgroup owns 1024 (q <= 8),
+// 2048 or 4096 (q > 24) sequences and one contiguous range of steps; it stages
 // each tile in LDS once (double-buffered through registers) and every
 // sequence picks J[(i, s_i), (j, s_j)] for its own tokens.  A step's 16
 // terms are summed in FP32 in column order, the step sums of a sub-range (a
@@ -26,13 +26,16 @@ namespace bmdca {
 // depend on the rest of the batch, on the workgroup size or on the form below.
 //
 // Small batches (fewer than kESplitBlocks workgroups otherwise, and room for
-// the sums) take a workgroup per sub-range and, up to kEFewSeqs sequences, one
-// sequence per thread; the finish then adds the sub-range sums of each range
+// the sums) take a workgroup per sub-range and, up to kEFewSeqs sequences and
+// kEFewBlocks workgroups, one sequence per thread; the finish then adds the sub-range sums of each range
 // first.  A workgroup's steps follow each other (fetch a tile, store it, look
 // up), about 2 us each, so a small call takes their number: 1003 sequences at
 // L = 123, q = 21, 16 ranges of 34 steps 84 us, 128 sub-ranges of 4 16 us; whole
 // calls, L = 200, 3000 sequences 122 -> 46 us, L = 60, 20 000 124 -> 34, q = 5,
-// L = 100, 1000 80 -> 18.  Where the ranges fill the device, sub-range sums
+// L = 100, 1000 80 -> 18.  More workgroups than that take turns on the CUs, each
+// with tiles of its own to load, and several sequences per thread are faster: L =
+// 512, q = 32, 2048 sequences 390 -> 171 us (by ranges 258), q = 21 187 -> 96.  Where
+// the ranges fill the device, sub-range sums
 // would be traffic for nothing, and the lookups bound the call: 64 random
 // 4-byte reads of LDS take 8.7 cycles (L = 512, q = 21, 1e5 sequences 2.9 ms).
 // ---------------------------------------------------------------------------
@@ -45,6 +48,7 @@ constexpr int energy_seqs(int Q) { return Q > 24 ? 8 : 4; }
 constexpr int kEFine = 8;  // sub-ranges per range
 constexpr int64_t kESplitBlocks = 256;
 constexpr int64_t kEFewSeqs = 2048;
+constexpr int64_t kEFewBlocks = 2048;
 // Threads per workgroup: 512 (2048 sequences) for q > 8, so that each staged
 // tile serves twice the lookups (a workgroup loads its own copy of every
 // tile; at q = 21 the tile stores were about 30% of the LDS traffic): L = 512,
@@ -394,7 +398,8 @@ static void launch_energy_q(const float* J, const int8_t* XT, int64_t B, int L,
                             const int64_t* count) {
   constexpr int T = energy_threads(Q);
   constexpr int KS = energy_seqs(Q);
-  const int seqs = plan.split && B <= kEFewSeqs ? 1 : KS;
+  const bool few = B <= kEFewSeqs && ceil_div(B, T) * plan.parts * kEFine <= kEFewBlocks;
+  const int seqs = plan.split && few ? 1 : KS;
   auto kern = !plan.split ? k_energy_pairs<Q, KS, false>
               : seqs == 1 ? k_energy_pairs<Q, 1, true>
                           : k_energy_pairs<Q, KS, true>;
