@@ -108,10 +108,11 @@ StatsPlan plan_stats(int64_t M, int L, int q, int prec) {
 __global__ __launch_bounds__(256) void k_transpose_tokens(const int8_t* __restrict__ X, int64_t M,
                                                           int L, int q, int8_t* __restrict__ XT,
                                                           int64_t Mpad, int32_t* dev_err,
-                                                          const int64_t* __restrict__ count) {
+                                                          const int64_t* __restrict__ count,
+                                                          int64_t first) {
   __shared__ int8_t t[64][65];
   if (count && *count < M) M = *count;
-  const int64_t m0 = (int64_t)blockIdx.x * 64;
+  const int64_t m0 = first + (int64_t)blockIdx.x * 64;
   if (m0 >= M) return;  // whole workgroup (its rows are not read), before the barrier
   const int i0 = blockIdx.y * 64;
   const int tx = threadIdx.x % 64, ty = threadIdx.x / 64;
@@ -178,8 +179,13 @@ __global__ __launch_bounds__(256) void k_transpose_tokens(const int8_t* __restri
 hipError_t launch_transpose_tokens(const int8_t* X, int64_t M, int L, int q, int8_t* XT,
                                   int64_t Mpad, int32_t* dev_err, hipStream_t s,
                                   const int64_t* count) {
-  hipLaunchKernelGGL(k_transpose_tokens, dim3((unsigned)(Mpad / 64), (unsigned)ceil_div(L, 64)),
-                     dim3(256), 0, s, X, M, L, q, XT, Mpad, dev_err, count);
+  // one launch per 2^23 workgroups (a grid dimension holds fewer than 2^32
+  // work-items: 2^30 rows would pass it)
+  const int64_t chunk = (int64_t)64 << 23;
+  for (int64_t m = 0; m < Mpad; m += chunk)
+    hipLaunchKernelGGL(k_transpose_tokens,
+                       dim3((unsigned)(std::min(chunk, Mpad - m) / 64), (unsigned)ceil_div(L, 64)),
+                       dim3(256), 0, s, X, M, L, q, XT, Mpad, dev_err, count, m);
   return hipGetLastError();
 }
 
@@ -577,8 +583,8 @@ hipError_t launch_onehot_products(const int8_t* X, const double* w, int64_t M, i
   float* wf = reinterpret_cast<float*>(base + plan.off_wf);
   double* P = reinterpret_cast<double*>(base + plan.off_part);
 
-  hipLaunchKernelGGL(k_transpose_tokens, dim3((unsigned)(plan.Mpad / 64), (unsigned)ceil_div(L, 64)),
-                     dim3(256), 0, s, X, M, L, q, XT, plan.Mpad, dev_err, nullptr);
+  const hipError_t e = launch_transpose_tokens(X, M, L, q, XT, plan.Mpad, dev_err, s);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_prep_weights, dim3((unsigned)ceil_div(plan.Mpad, 256)), dim3(256), 0, s, w,
                      M, plan.Mpad, whi, wlo, wf);
   switch (mode_of(prec, w != nullptr)) {

@@ -8,9 +8,10 @@ from paper_2501_18456_amd import _lib, api
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("live", [None, (1 << 29) + 65])
-def test_energies_of_more_than_2_to_29_sequences(live):
-    B, L, q = (1 << 29) + 70, 2, 4
+@pytest.mark.parametrize("B,live", [((1 << 29) + 70, None), ((1 << 29) + 70, (1 << 29) + 65),
+                                    ((1 << 30) + 70, None), ((1 << 30) + 70, (1 << 30) + 65)])
+def test_energies_of_more_than_2_to_29_sequences(B, live):
+    L, q = 2, 4
     g = torch.Generator(device="cuda")
     g.manual_seed(29)
     # multiples of 2^-10: the sums of Eq. (1) are exact, so are the energies
