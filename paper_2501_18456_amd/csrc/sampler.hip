@@ -16,8 +16,8 @@ namespace bmdca {
 // token = (word * q) >> 32.
 // ---------------------------------------------------------------------------
 __global__ void k_init_chains(int8_t* __restrict__ chains, int64_t N, int L, int q, uint32_t k0,
-                              uint32_t k1) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                              uint32_t k1, int64_t first) {
+  const int64_t idx = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= N * (int64_t)L) return;
   const int64_t c = idx / L;
   const int i = (int)(idx % L);
@@ -30,8 +30,11 @@ hipError_t launch_init_chains(int8_t* chains, int64_t N, int L, int q, uint64_t 
                               hipStream_t s) {
   const int64_t total = N * (int64_t)L;
   const int bs = 256;
-  hipLaunchKernelGGL(k_init_chains, dim3((unsigned)ceil_div(total, bs)), dim3(bs), 0, s, chains,
-                     N, L, q, (uint32_t)seed, (uint32_t)(seed >> 32));
+  // one launch per 2^31 cells (a grid dimension holds fewer than 2^32 work-items)
+  const int64_t chunk = (int64_t)1 << 31;
+  for (int64_t c = 0; c < total; c += chunk)
+    hipLaunchKernelGGL(k_init_chains, dim3((unsigned)ceil_div(std::min(chunk, total - c), bs)),
+                       dim3(bs), 0, s, chains, N, L, q, (uint32_t)seed, (uint32_t)(seed >> 32), c);
   return hipGetLastError();
 }
 
