@@ -45,9 +45,9 @@ GATHER_TRAFFIC_SOURCES = ("paper_2501_18456_amd/csrc/gather_kernel.hpp",
                           "paper_2501_18456_amd/csrc/common.hpp")
 # workload -> bytes per launch: the gather kernel's 10-sweep launch and the
 # field kernel's 5-sweep launch of the precision form (L = 256, N = 20 000)
-GATHER_TRAFFIC = {"sha256": "3c482659c4ac98d49a2e726350f4bb1266cf3b65cc06db29ee0cfd5134c89a39",
-                  "bytes": {"precision": 1.25806e+10,           # 1.25754e+10 read + 5.18e6 written
-                            "precision-fields": 1.98288e12}}  # 1.46101e12 read + 5.2187e+11
+GATHER_TRAFFIC = {"sha256": "9a7033c7486d00a9fcbc0d0155b3867b66fa8ebf7d9beb134154876ac8eba2b8",
+                  "bytes": {"precision": 1.24571e+10,           # 1.24519e+10 read + 5.18483e+06 written
+                            "precision-fields": 1.9837e+12}}  # 1.46188e+12 read + 5.21818e+11
 
 
 def sources_digest():
@@ -335,7 +335,7 @@ def bench_protein(args, emit=True):
         "config": {"workload": "bmDCA training epoch at protein scale", "L": L, "q": q,
                    "chains": N, "msa_rows": M, "sweeps_per_step": sweeps, "lr": lr,
                    "stats_precision": args.prec, "reweight_identity": 0.8},
-        "roofline": {"kernel": "k_gibbs_gather (Gibbs sweeps, gather form)", "bound": "lds",
+        "roofline": {"kernel": "k_gibbs_free (Gibbs sweeps, gather form)", "bound": "lds",
                      "achieved": lds_gbs, "peak": lds_peak, "unit": "GB/s",
                      "frac": lds_gbs / lds_peak, "traffic": gather_traffic("protein"),
                      "launch_ms": g_ms, "alg_bytes_per_launch": lds_bytes},
@@ -619,7 +619,7 @@ def bench_next(args):
         "config": {"workload": "equilibrium sampling, Metropolis sweeps, element "
                                "decimation and activation at protein scale", "L": L, "q": q, "chains": N,
                    "msa_rows": M, "sweeps_per_step": sweeps},
-        "roofline": {"kernel": "k_gibbs_gather (Metropolis sweeps, gather form)",
+        "roofline": {"kernel": "k_gibbs_free (Metropolis sweeps, gather form)",
                      "bound": "lds", "achieved": lds_gbs, "peak": lds_peak, "unit": "GB/s",
                      "frac": lds_gbs / lds_peak, "traffic": None, "launch_ms": mg_ms,
                      "alg_bytes_per_launch": lds_bytes},
@@ -863,7 +863,7 @@ def bench_precision_epoch(args):
                                "M=100000 weighted rows, N=20000 chains",
                    "L": L, "q": q, "msa_rows": M, "chains": N, "sweeps_per_step": sweeps,
                    "lr": lr, "step_form": "fp32 (BF16 hi+lo epoch in extras)"},
-        "roofline": {"kernel": "k_gibbs_gather (Gibbs sweeps, gather form)", "bound": "lds",
+        "roofline": {"kernel": "k_gibbs_free (Gibbs sweeps, gather form)", "bound": "lds",
                      "achieved": lds_gbs, "peak": lds_peak, "unit": "GB/s",
                      "frac": lds_gbs / lds_peak, "traffic": gather_traffic("precision"),
                      "launch_ms": g_ms, "alg_bytes_per_launch": lds_bytes,

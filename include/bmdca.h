@@ -230,10 +230,10 @@ typedef struct bmdca_chain_stream {
  * fields of the gather form are summed in an order fixed by L, q and the draw
  * (the lanes per chain are a function of q and the draw alone; heat-bath
  * chains with 5..7 quads per row may run narrow, one lane per quad, where a
- * launch has many chains per CU, and draw the same bits; launches with many
- * chains per workgroup take one barrier per two chunk-steps, which changes no
- * arithmetic), so heat-bath chains are bit-identical to their alone call in
- * any launch.  For
+ * launch has many chains per CU, and draw the same bits; a workgroup per chain
+ * where a launch has few chains, waves that run free of each other or in step
+ * else, which changes no arithmetic), so heat-bath chains are bit-identical to
+ * their alone call in any launch.  For
  * Metropolis the order also follows the chunk length, which the chains per
  * workgroup bound where their tokens fill the LDS; where two launches differ
  * in it a chain can part from its alone trajectory at a draw within FP32
@@ -274,7 +274,9 @@ int bmdca_energy(const float* h, const float* J, const int8_t* seqs, int64_t B,
  * pair sums, align256(L Bp) + align256(8 P Bp) bytes with Bp = B rounded up
  * to 64 and P <= 128 pair ranges fixed by L) lives in one static device array
  * of BMDCA_ENERGY_SCRATCH_BYTES per GPU, held from library load to process
- * end; nothing in it needs clearing between calls.  A batch whose scratch
+ * end; nothing in it needs clearing between calls.  (A small batch sums its
+ * ranges in eight parts where the array holds eight times the partial sums;
+ * the energies are the same bits.)  A batch whose scratch
  * exceeds the array returns BMDCA_EINVAL before anything is enqueued (up
  * to 43 648 sequences fit at L = 512, 84 672 at L = 256, 328 960 at
  * L = 100): split it, or call bmdca_energy.  Every call on one GPU uses the
@@ -481,7 +483,9 @@ int bmdca_activate(uint8_t* mask, const int8_t* chains, int64_t N, int32_t L,
  *               = -(H_i(a) - H_i(wt_i)),  H_i(a) = h_i(a) + sum_{j!=i} J_ij(a, wt_j);
  * dE is exactly 0 at a = wt_i.
  * wt int8 [B][L]; dE float32 [B][Lq] out.
- * ws scratch, bmdca_workspace_bytes(BMDCA_WS_MUTANT, B, L, q, 0). */
+ * ws bmdca_workspace_bytes(BMDCA_WS_MUTANT, B, L, q, 0) bytes.  Required, and
+ *    of that size (BMDCA_EWORKSPACE if smaller), though the scan keeps its local
+ *    fields on chip: it is neither read nor written. */
 int bmdca_single_mutant_scan(const float* h, const float* J, const int8_t* wt,
                              int64_t B, int32_t L, int32_t q, float* dE,
                              void* ws, size_t ws_bytes, void* stream);
@@ -518,7 +522,8 @@ int bmdca_energy_batch(const float* h, const float* J, const int8_t* seqs, int64
                        size_t ws_bytes, int32_t* dev_err, void* stream);
 
 /* bmdca_single_mutant_scan over wild types wt [cap][L] (first *n_live live);
- * ws sized by bmdca_workspace_bytes(BMDCA_WS_MUTANT, cap, L, q, 0). */
+ * ws sized by bmdca_workspace_bytes(BMDCA_WS_MUTANT, cap, L, q, 0) (required as
+ * there, not touched). */
 int bmdca_mutant_scan_batch(const float* h, const float* J, const int8_t* wt, int64_t cap,
                             const int64_t* n_live, int32_t L, int32_t q, float* dE, void* ws,
                             size_t ws_bytes, void* stream);

@@ -46,7 +46,7 @@ struct GatherShape {
   int slot;       // floats per ring slot (nload * items KB)
   size_t lds;     // dynamic LDS bytes
   unsigned blocks;
-  int pair;       // 1: paired chunk-steps (one barrier per two steps, two chunks in flight)
+  int pair;       // gather_pair() of the shape; read by no kernel
 };
 
 // Token bytes per chain.
@@ -70,10 +70,13 @@ inline GatherShape gather_shape_n(int L, int q, int cpb, int nslot, int lpc, boo
   const size_t per_slot = std::min((kGLds - tok) / nslot, (size_t)31 * g.waves * 1024);
   // Chunks are a multiple of 4 S sites (4 token positions per lane, one
   // token dword) and of kGAlign bytes: a chunk that starts off a 128-byte
-  // boundary of the run makes every load of it misaligned (L = 100, q = 21:
-  // 17-site chunks, 34272 bytes, took 1.8x the time per sweep of 16-site
-  // ones).  A 256-byte rule costs steps for nothing: at q = 21 it takes
-  // 8-site chunks where 12 fit (L = 512: 64 chunk-steps per site instead of
+  // boundary of the run makes every load of it misaligned.  Aligned and not, in
+  // free-running waves, ms, 3 sweeps: q = 19, L = 300, 6000 chains, 16- and
+  // 20-site chunks, 7.96 and 8.45, 10 000 chains 8.63 and 8.95; q = 17, L = 100,
+  // 24- and 20-site chunks, 5 sweeps, 1.77 and 1.73 (few chunk lengths are
+  // affected: rows of q = 21 or 13 are aligned by the token rule alone).  A
+  // 256-byte rule costs steps for nothing: at q = 21 it takes 8-site chunks
+  // where 12 fit (with barriers at L = 512: 64 chunk-steps per site instead of
   // 43; 39.6 against 25.0 ms per sweep for 10 000 chains on 32 CUs).
   int step = 4 * S;
   while (align && ((size_t)step * site_row) % kGAlign != 0) step += 4 * S;
@@ -103,9 +106,10 @@ inline GatherShape gather_shape_n(int L, int q, int cpb, int nslot, int lpc, boo
   return GatherShape{};
 }
 
-// A ring of 4 slots: three chunks in flight.  Measured at L = 100..512,
-// q = 21: 3 slots (larger chunks, two in flight) take 1.4-1.8x as long per
-// sweep, 5, 6 or 8 slots (smaller chunks, more steps) 1.5-2.5x.
+// A ring of 4 slots: three chunks in flight.  Measured with barriers at L =
+// 100..512, q = 21: 3 slots (larger chunks, two in flight) take 1.4-1.8x as
+// long per sweep, 5, 6 or 8 slots (smaller chunks, more steps) 1.5-2.5x (not
+// measured in free-running waves).
 inline GatherShape gather_shape(int L, int q, int cpb, int lpc) {
   const GatherShape g = gather_shape_n(L, q, cpb, 4, lpc, true);
   // unaligned chunks only where no aligned shape fits (q = 25 or 27 at large
@@ -117,14 +121,12 @@ inline GatherShape gather_shape(int L, int q, int cpb, int lpc) {
 // the chain count or the CU share, because the FP32 summation order of a
 // chain's local fields follows its lanes -- with this rule a chain draws the
 // same bits in bmdca_gibbs, in a grouped epoch on a CU share and in a merged
-// bmdca_gibbs_streams launch.  8 lanes for q > 8 (16 cost 1.9x at q = 21:
-// the per-wave step overhead doubles).  For q <= 8 (rows of at most two
-// quads) the heat-bath draw also takes 8: its 8-wave kernel reads tokens a
-// step ahead, which outweighs the halved lanes (q = 5, L = 400, 10 000
-// chains: 23.6 against 28.2 ms per 10 sweeps; q = 8, L = 60: 0.78 against
-// 1.16; with 4096 chains on the whole device 16 lanes were 13% faster, the
-// price of the fixed rule).  Metropolis, which runs the 16-wave kernel,
-// takes 16 (q = 5, L = 400, 10 000 chains: 24.0 against 27.2 ms).
+// bmdca_gibbs_streams launch.  So the lanes are part of the results, and stay
+// whatever a kernel would favour: 8, and 16 for Metropolis at q <= 8 (rows of
+// at most two quads).  They were taken from a form with barriers: 16 lanes cost
+// 1.9x at q = 21, where the per-wave step overhead doubles; at q = 5, L = 400,
+// 10 000 chains the heat bath took 23.6 ms per 10 sweeps with 8 and 28.2 with
+// 16, Metropolis 27.2 and 24.0.
 constexpr int gather_lanes(int q, bool small) { return (gather_v(q) <= 2 && !small) ? 16 : 8; }
 
 // Narrow heat-bath chains: rows of 5, 6 or 7 quads (q = 17..28) can also run
@@ -134,35 +136,31 @@ constexpr int gather_lanes(int q, bool small) { return (gather_v(q) <= 2 && !sma
 // the draw's cross-lane steps keep the 8-lane association order, so a narrow
 // chain draws the same bits as an 8-lane one (checked over whole runs): the
 // choice may follow the launch shape.  The planner takes it where it saves
-// waves and still leaves at least kGNarrowWaves, two per SIMD (L = 256,
-// q = 21, 20 000 chains: 8 waves instead of 10, 33.5 against 39.6 ms per 10
-// sweeps; with one wave per SIMD it lost: L = 100, 10 000 chains, 4 instead
-// of 5 waves, 5.71 against 5.45 ms; 7 instead of 8 waves was mixed, 16 384
-// chains: +2.4% at L = 100, +1.3% at L = 256, -3.9% at L = 512).
+// waves and still leaves at least kGNarrowWaves, two per SIMD.  Free-running
+// waves, 8 lanes -> narrow, ms, 3 sweeps of q = 21, with 8 narrow waves or more:
+// 18 000 chains (9 waves -> 8) L = 60 0.62 -> 0.61, L = 100 1.54 -> 1.47, L =
+// 256 9.26 -> 7.93, L = 512 42.7 -> 34.6; 30 000 (15 -> 12) 0.80 -> 0.77, 2.11
+// -> 1.93, 13.0 -> 11.1, 58.2 -> 47.0; 24 000 (12 -> 10), the weakest, 0.65 ->
+// 0.71, 1.66 -> 1.77, 10.0 -> 10.1, 45.4 -> 43.5; q = 17, L = 100 15-18%
+// faster, q = 25, L = 256 even to 17% faster.  With fewer: 16 384 (8 -> 7)
+// 0.48 -> 0.59, 1.26 -> 1.44, 7.30 -> 7.85, 33.6 -> 34.2, 12 000 (6 -> 5) 0.47
+// -> 0.53, 1.18 -> 1.31, 6.60 -> 6.76, 27.1 -> 27.0, 10 000 (5 -> 4) 0.47 ->
+// 0.50, 1.16 -> 1.18, 6.39 -> 6.08, 27.1 -> 27.0: a wave that is there to hide
+// another's draw is worth more than the idle lanes.
 constexpr int kGNarrowWaves = 8;
 constexpr int gather_narrow_lanes(int q, bool small) {
   return (small && gather_v(q) == 8 && gather_qp(q) / 4 < 8) ? gather_qp(q) / 4 : 0;
 }
 
-// Paired chunk-steps (of the form with barriers, which plans of 16 waves run, all
-// of them paired by this rule; free-running waves have no steps to pair): the
-// ring of 4 slots is refilled two chunks at a time,
-// one wait and one barrier per two steps, with two chunks in flight instead
-// of three.  Where a workgroup holds at least this many chains the row
-// gathers dominate a step and the halved barriers pay (L = 256, q = 21,
-// 20 000 chains: 33.6 -> 30.2 ms per 10 sweeps; L = 100, 10 000 chains
-// 5.46 -> 5.27; q = 12, L = 200 11.4 -> 10.0; q = 5, L = 400 17.8 -> 16.0;
-// Metropolis sweeps, whose staging is most of the step: L = 100 4.30 -> 3.96,
-// L = 256 24.0 -> 21.9, q = 5, L = 400 24.2 -> 22.4, q = 12, L = 200
-// 9.14 -> 8.52);
-// with fewer the staging latency dominates and the third chunk in flight
-// pays more (L = 512, 4096 chains, 16 per workgroup: 114.7 against 130.8).
-// The same holds where the re-laid-out couplings (L^2 q QP 4 bytes) exceed
-// the 256 MB last-level cache and the staging comes from HBM, unless the
-// workgroup holds at least twice as many chains (10 000 chains, 40 per
-// workgroup: L = 400 (323 MB) 71.0 against 79.9 ms, L = 512 (528 MB) 115.3
-// against 130.3; L = 300 (181 MB) 41.0 against 40.6; L = 512, 20 000 chains,
-// 80 per workgroup: 254.9 against 246.2).  The chains draw the same bits either way.
+// Whether a plan's chunk-steps would be worth pairing in the form with barriers:
+// the ring of 4 slots refilled two chunks at a time, one wait and one barrier per
+// two steps, two chunks in flight instead of three.  No kernel reads it: the form
+// with barriers runs plans of many waves, pairs always, and free-running waves
+// have no steps to pair.  A launch on a share of the CUs pairs as well; it runs
+// Metropolis of q <= 8 in plans of 16 waves, ms unpaired -> paired: 32 CUs, q = 5,
+// 2048 chains L = 100 2.95 -> 2.76, L = 400 38.9 -> 37.7, q = 4, L = 200, 1024
+// chains on 16 CUs 11.6 -> 11.2; epochs of 32 models at q = 5 55.2 -> 52.5, q = 8
+// 66.3 -> 64.3, q = 4 98.8 -> 91.3, of 64 models 113.5 -> 108.4.
 constexpr int kGPairChains = 32;
 constexpr double kGPairCacheBytes = 256.0 * 1024 * 1024;
 inline int gather_pair(int L, int q, int cpb) {
