@@ -63,8 +63,8 @@ __global__ void k_draw_rows(const double* __restrict__ C, int64_t M, int64_t n, 
 // BMDCA_DEVERR_INDEX and copies row 0.
 __global__ void k_gather_rows(const int8_t* __restrict__ X, int64_t M, int L,
                               const int32_t* __restrict__ rows, int64_t n,
-                              int8_t* __restrict__ out, int32_t* dev_err) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                              int8_t* __restrict__ out, int32_t* dev_err, int64_t first) {
+  const int64_t e = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n * L) return;
   const int64_t k = e / L;
   const int i = (int)(e % L);
@@ -160,8 +160,11 @@ hipError_t launch_draw_rows(const double* w, int64_t M, int64_t n, uint64_t seed
 hipError_t launch_gather_rows(const int8_t* X, int64_t M, int L, const int32_t* rows, int64_t n,
                               int8_t* out, int32_t* dev_err, hipStream_t s) {
   const int64_t total = n * L;
-  hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, s, X, M, L,
-                     rows, n, out, dev_err);
+  // one launch per 2^31 cells (a grid dimension holds fewer than 2^32 work-items)
+  const int64_t chunk = (int64_t)1 << 31;
+  for (int64_t e = 0; e < total; e += chunk)
+    hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)ceil_div(std::min(chunk, total - e), 256)),
+                       dim3(256), 0, s, X, M, L, rows, n, out, dev_err, e);
   return hipGetLastError();
 }
 
