@@ -158,13 +158,14 @@ __global__ __launch_bounds__(WPB * 64) void k_gibbs_hbm(const float* __restrict_
                                                         unsigned long long* flips_out,
                                                         const uint64_t* __restrict__ epoch,
                                                         const int32_t* __restrict__ active,
-                                                        const ChainStream* __restrict__ streams) {
+                                                        const ChainStream* __restrict__ streams,
+                                                        int64_t first) {
   if (active && *active == 0) return;
   if (epoch) sweep_offset += *epoch * (uint64_t)sweeps;
   extern __shared__ int8_t tok_all[];
   const int lane = threadIdx.x % kWave;
   const int wid = threadIdx.x / kWave;
-  const int64_t c = (int64_t)blockIdx.x * WPB + wid;
+  const int64_t c = first + (int64_t)blockIdx.x * WPB + wid;
   if (c >= N) return;  // whole wave leaves; no block barriers below
   uint32_t cid = (uint32_t)c;
   if (streams) {
@@ -243,9 +244,13 @@ hipError_t launch_gibbs_sweeps(const float* J, int8_t* chains, float* H, int64_t
   constexpr int WPB = 4;
   const int Lpad = (L + 3) & ~3;
   auto kern = metropolis ? k_gibbs_hbm<WPB, true> : k_gibbs_hbm<WPB, false>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(N, WPB)), dim3(WPB * kWave), WPB * Lpad, s, J,
-                     chains, H, N, L, q, sweeps, (uint32_t)seed, (uint32_t)(seed >> 32),
-                     sweep_offset, beta, flips_out, ctl.epoch, ctl.active, ctl.streams);
+  // one launch per 2^25 chains (a grid dimension holds fewer than 2^32 work-items)
+  const int64_t chunk = (int64_t)1 << 25;
+  for (int64_t c = 0; c < N; c += chunk)
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(std::min(chunk, N - c), WPB)),
+                       dim3(WPB * kWave), WPB * Lpad, s, J, chains, H, N, L, q, sweeps,
+                       (uint32_t)seed, (uint32_t)(seed >> 32), sweep_offset, beta, flips_out,
+                       ctl.epoch, ctl.active, ctl.streams, c);
   return hipGetLastError();
 }
 
