@@ -37,8 +37,9 @@ __global__ __launch_bounds__(256) void k_prefix_weights(const double* __restrict
 // non-decreasing prefix sums).  A total that is not positive and finite
 // raises BMDCA_DEVERR_NONFINITE and yields row 0.
 __global__ void k_draw_rows(const double* __restrict__ C, int64_t M, int64_t n, uint32_t k0,
-                            uint32_t k1, int32_t* __restrict__ rows, int32_t* dev_err) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                            uint32_t k1, int32_t* __restrict__ rows, int32_t* dev_err,
+                            int64_t first) {
+  const int64_t k = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   const double W = C[M - 1];
   if (!(W > 0.0) || !isfinite(W)) {
@@ -151,9 +152,11 @@ hipError_t launch_draw_rows(const double* w, int64_t M, int64_t n, uint64_t seed
                             void* ws, int32_t* dev_err, hipStream_t s) {
   double* C = static_cast<double*>(ws);
   hipLaunchKernelGGL(k_prefix_weights, dim3(1), dim3(256), 0, s, w, M, C);
-  if (n > 0)
-    hipLaunchKernelGGL(k_draw_rows, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, C, M, n,
-                       (uint32_t)seed, (uint32_t)(seed >> 32), rows, dev_err);
+  // one launch per 2^31 draws (a grid dimension holds fewer than 2^32 work-items)
+  const int64_t chunk = (int64_t)1 << 31;
+  for (int64_t k = 0; k < n; k += chunk)
+    hipLaunchKernelGGL(k_draw_rows, dim3((unsigned)ceil_div(std::min(chunk, n - k), 256)), dim3(256),
+                       0, s, C, M, n, (uint32_t)seed, (uint32_t)(seed >> 32), rows, dev_err, k);
   return hipGetLastError();
 }
 
