@@ -45,9 +45,9 @@ GATHER_TRAFFIC_SOURCES = ("paper_2501_18456_amd/csrc/gather_kernel.hpp",
                           "paper_2501_18456_amd/csrc/common.hpp")
 # workload -> bytes per launch: the gather kernel's 10-sweep launch and the
 # field kernel's 5-sweep launch of the precision form (L = 256, N = 20 000)
-GATHER_TRAFFIC = {"sha256": "8290d9b02030b43f743bb5a96dde4dc9d77c2f4b0430c6fc370ede5011afc2f2",
-                  "bytes": {"precision": 1.25122e+10,           # 1.2507e+10 read + 5.18483e+06 written
-                            "precision-fields": 1.98243e+12}}  # 1.46059e+12 read + 5.21844e+11
+GATHER_TRAFFIC = {"sha256": "aa90385f7b368c8026a7d16902301f4a5b52fd8ac439b861a394688a753cfde2",
+                  "bytes": {"precision": 1.27571e+10,           # 1.2752e+10 read + 5.18483e+06 written
+                            "precision-fields": 1.98057e+12}}  # 1.45872e+12 read + 5.21849e+11
 
 
 def sources_digest():

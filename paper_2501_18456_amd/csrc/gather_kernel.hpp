@@ -186,13 +186,14 @@ __global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_gather(
   if (run && *run == 0) return;  // whole grid leaves before any barrier
   // With a live count (a launch sized for N chains of which the first *count
   // are live) the workgroups take chains strided by the grid, chain
-  // cb * gridDim.x + blockIdx.x, so a partly filled arena still spreads its
-  // live chains over every workgroup; otherwise each takes a contiguous range.
+  // cb * nblk + blk, so a partly filled arena still spreads its live chains over
+  // every workgroup; otherwise each takes a contiguous range.
+  const uint32_t nblk = gridDim.x * gridDim.y, blk = blockIdx.y * gridDim.x + blockIdx.x;
   if (count) {
     const int64_t live = *count;
     if (live < N) N = live;
   }
-  if ((count ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * cpb) >= N)
+  if ((count ? (int64_t)blk : (int64_t)blk * cpb) >= N)
     return;  // no live chain: whole workgroup, before any barrier
   if (epoch) sweep_offset += *epoch * (uint64_t)sweeps;
   constexpr int QP = gather_qp(Q), NQ = QP / 4, V = gather_v(Q), S = gather_s(Q, LPC);
@@ -208,8 +209,7 @@ __global__ __launch_bounds__(kGMaxWaves * 64) void k_gibbs_gather(
   float* ring = reinterpret_cast<float*>(g_smem);                             // [nslot][slot]
   uint32_t* tokw = reinterpret_cast<uint32_t*>(ring + (size_t)nslot * slot);  // [S][m4][CPB]
   unsigned char* tokb = reinterpret_cast<unsigned char*>(tokw);
-  const int64_t c =
-      count ? (int64_t)cb * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * cpb + cb;
+  const int64_t c = count ? (int64_t)cb * nblk + blk : (int64_t)blk * cpb + cb;
   const bool has_chain = cb < cpb;
   const bool active = has_chain && (c < N);
   const bool reader = has_chain && v < NQ;
@@ -646,9 +646,12 @@ hipError_t launch_gather_shape(const GatherShape& gs, const GatherArgs& a) {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)gs.lds);
   if (e != hipSuccess) return e;
   const DevCtl& ctl = *a.ctl;
-  hipLaunchKernelGGL(kern, dim3(gs.blocks), dim3(gs.waves * 64), gs.lds, a.s, a.h, a.Jt, a.chains,
-                     a.N, a.L, gs.jc, gs.nchunk, gs.m4, gs.ahead, gs.nload, gs.slot, gs.cpb,
-                     a.sweeps, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), a.sweep_offset, a.beta,
+  // 2^21 workgroups a row of the grid, as in the free-running form
+  const unsigned gx = std::min(gs.blocks, 1u << 21);
+  const dim3 grid(gx, (unsigned)gp_ceil(gs.blocks, gx));
+  hipLaunchKernelGGL(kern, grid, dim3(gs.waves * 64), gs.lds, a.s, a.h, a.Jt, a.chains, a.N, a.L,
+                     gs.jc, gs.nchunk, gs.m4, gs.ahead, gs.nload, gs.slot, gs.cpb, a.sweeps,
+                     (uint32_t)a.seed, (uint32_t)(a.seed >> 32), a.sweep_offset, a.beta,
                      a.flips_out, a.dev_err, ctl.epoch, ctl.active, ctl.streams, ctl.count);
   return hipGetLastError();
 }
